@@ -6,9 +6,11 @@
 //   Sec. 5.5), the update buffer (Sec. 5.3) and heterogeneous double
 //   compression buffering (Sec. 5.4).
 //
-// Work decomposition: the prefill runs one 256-thread workgroup per 64-token
-// segment, wave w owning tokens [16w, 16w+16); the append path's flush and
-// finalize run 16-token workgroups of 8 waves x 2 tokens.  Lane l owns
+// Work decomposition: the prefill's encoding kernel for kept counts of 16, 32
+// and 48 is in encode.hip.  For other counts the prefill runs one 256-thread
+// workgroup per 64-token segment, wave w owning tokens [16w, 16w+16); the
+// append path's flush and finalize run 16-token workgroups of 8 waves x 2
+// tokens.  Lane l owns
 // channels l and l+64, so a vector's 128 channels live in one wave and
 // channel trees, ranks, bitmaps and slot numbers are wave-local (butterflies,
 // ballots, mbcnt).  The rotation is an fp32 fused-multiply-add chain over
@@ -995,19 +997,29 @@ hipError_t launch_copy_rot(const Geom &g, const float *rk, const float *rv, int 
     return hipGetLastError();
 }
 
+// The prefill kernels (mode as in k_prefill).  Kept counts of 16, 32 and 48
+// take the lane-per-token kernel of encode.hip; other counts the ranks here,
+// which need no fixed position in a sorted list.
+static hipError_t launch_prefill(const Geom &g, int mode, const uint16_t *k, const uint16_t *v, int64_t seq_stride,
+                                 uint8_t *ws, uint32_t slot_tok, uint32_t slot_sc, int segs, int close, hipStream_t s) {
+    if (encode_fits(g)) return launch_encode(g, mode, k, v, seq_stride, ws, slot_tok, slot_sc, segs, close, s);
+    const dim3 grid(segs, g.npairs);
+    if (mode == 0) hipLaunchKernelGGL(k_prefill<0>, grid, dim3(256), 0, s, g, k, v, seq_stride, ws, slot_tok, slot_sc, close);
+    else if (mode == 1) hipLaunchKernelGGL(k_prefill<1>, grid, dim3(256), 0, s, g, k, v, seq_stride, ws, slot_tok, slot_sc, close);
+    else hipLaunchKernelGGL(k_prefill<2>, grid, dim3(256), 0, s, g, k, v, seq_stride, ws, slot_tok, slot_sc, close);
+    return hipGetLastError();
+}
+
 hipError_t launch_close(const Geom &g, const float *rk, const float *rv, const uint16_t *k, const uint16_t *v,
                         int64_t seq_stride, int max_segs, hipStream_t s) {
     hipLaunchKernelGGL(k_close_rot, dim3(2, g.npairs), dim3(256), 0, s, g, rk, rv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 grid(max_segs, g.npairs);
     if (max_segs > 0) {
-        hipLaunchKernelGGL(k_prefill<0>, grid, dim3(256), 0, s, g, k, v, seq_stride, (uint8_t *)nullptr, 0u, 0u, 1);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_prefill(g, 0, k, v, seq_stride, nullptr, 0u, 0u, max_segs, 1, s)) != hipSuccess) return e;
         hipLaunchKernelGGL(k_scan, dim3(g.npairs), dim3(256), 0, s, g, 1);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_prefill<1>, grid, dim3(256), 0, s, g, k, v, seq_stride, (uint8_t *)nullptr, 0u, 0u, 1);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_prefill(g, 1, k, v, seq_stride, nullptr, 0u, 0u, max_segs, 1, s)) != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_close_done, dim3(ceil_div(g.npairs, 256)), dim3(256), 0, s, g);
     return hipGetLastError();
@@ -1029,15 +1041,14 @@ hipError_t launch_compress(const Geom &g, const uint16_t *k, const uint16_t *v, 
     }
     const dim3 grid(max_full_segs, g.npairs);
     if (max_full_segs > 0) {
-        if (ws) hipLaunchKernelGGL(k_prefill<2>, grid, dim3(256), 0, s, g, k, v, seq_stride, ws, slot_tok, slot_sc, 0);
-        else hipLaunchKernelGGL(k_prefill<0>, grid, dim3(256), 0, s, g, k, v, seq_stride, ws, slot_tok, slot_sc, 0);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_prefill(g, ws ? 2 : 0, k, v, seq_stride, ws, slot_tok, slot_sc, max_full_segs, 0, s)) != hipSuccess)
+            return e;
     }
     hipLaunchKernelGGL(k_scan, dim3(g.npairs), dim3(256), 0, s, g, 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (max_full_segs > 0) {
         if (ws) hipLaunchKernelGGL(k_compact, grid, dim3(256), 0, s, g, (const uint8_t *)ws, slot_tok, slot_sc);
-        else hipLaunchKernelGGL(k_prefill<1>, grid, dim3(256), 0, s, g, k, v, seq_stride, ws, slot_tok, slot_sc, 0);
+        else launch_prefill(g, 1, k, v, seq_stride, ws, slot_tok, slot_sc, max_full_segs, 0, s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (any_tail) {

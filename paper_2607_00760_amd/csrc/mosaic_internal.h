@@ -256,6 +256,11 @@ hipError_t launch_close(const Geom &g, const float *rk, const float *rv, const u
 hipError_t launch_compress(const Geom &g, const uint16_t *k, const uint16_t *v, int64_t seq_stride,
                            const int32_t *ctx_dev, int max_full_segs, int any_tail, uint8_t *ws, uint32_t slot_tok,
                            uint32_t slot_sc, hipStream_t s);
+// the encoding kernel for kept counts of 16, 32 and 48 (mode 0: strategy, 1:
+// pack at the descriptor's offsets, 2: both, into workspace slots)
+bool encode_fits(const Geom &g);
+hipError_t launch_encode(const Geom &g, int mode, const uint16_t *k, const uint16_t *v, int64_t seq_stride, uint8_t *ws,
+                         uint32_t slot_tok, uint32_t slot_sc, int segs, int close, hipStream_t s);
 hipError_t launch_set_meta(const Geom &g, const int32_t *ctx_dev, hipStream_t s);
 hipError_t launch_append(const Geom &g, const uint16_t *k, const uint16_t *v, hipStream_t s);
 // what: MAINT_FLUSH and / or MAINT_FINALIZE, the kernels to launch (each
