@@ -116,7 +116,7 @@ def algorithmic_bytes(cache, spec, nb_list, sel_list, desc_list):
 
 def source_hash():
     h = hashlib.sha256()
-    for f in ("decode.hip", "mosaic_internal.h"):
+    for f in ("attn.h", "decode.hip", "decode_common.h", "dense_step.h", "mosaic_internal.h", "score.hip"):
         h.update(open(os.path.join(ROOT, "paper_2607_00760_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -15,7 +15,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmosaic.so")
 ARCH = os.environ.get("MOSAIC_OFFLOAD_ARCH", "gfx950")
-SOURCES = ["api.hip", "compress.hip", "decode.hip", "dense.hip", "encode.hip", "rotation.hip"]
+SOURCES = ["api.hip", "attn_bf16_g4.hip", "attn_bf16_g8.hip", "attn_fp16_g4.hip", "attn_fp16_g8.hip", "compress.hip",
+           "decode.hip", "dense.hip", "encode.hip", "rotation.hip", "score.hip"]
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -45,7 +46,7 @@ def build(verbose: bool = False) -> str:
             sys.stderr.write(r.stderr)
         return obj
 
-    with cf.ThreadPoolExecutor(max_workers=min(6, os.cpu_count() or 1)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()
     r = subprocess.run([hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs],

@@ -15,6 +15,9 @@ constexpr int WAVE = 64;
 // block table)
 constexpr int SPLIT_MIN = 48;
 constexpr int SPLIT_MAX = 128;
+constexpr int SPLIT_LEAST = 8;    // blocks of the smallest split (short selections; see the attention's plan)
+constexpr int ATTN_NWV = 2;       // waves per attention workgroup
+constexpr int ATTN_WPE = 2;       // waves per SIMD the attention's registers allow
 constexpr int MAX_WINDOWS = 1024;  // rotation windows per sequence (the selection tracks them in LDS)
 constexpr int SCORE_SEGS = 128;    // segments per block-scoring workgroup (one launch round)
 constexpr int CMB_COLS = 16;                  // output columns per combine workgroup
@@ -268,6 +271,13 @@ hipError_t launch_append(const Geom &g, const uint16_t *k, const uint16_t *v, hi
 hipError_t launch_maintain(const Geom &g, int mode, int what, hipStream_t s);
 hipError_t launch_decode(const Geom &g, const WsGeom &w, const uint16_t *q, float *out, float scale,
                          int max_desc_used, int max_windows_used, hipStream_t s, hipEvent_t *ev);
+// the decode step's scoring and attention; fixed: every possible kept count is
+// 16, 32 or 48, small: none exceeds 48
+hipError_t launch_score(const Geom &g, const WsGeom &w, int max_desc_used, bool fixed, bool small, hipStream_t s);
+hipError_t launch_attn_bf16_g4(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s);
+hipError_t launch_attn_bf16_g8(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s);
+hipError_t launch_attn_fp16_g4(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s);
+hipError_t launch_attn_fp16_g8(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s);
 hipError_t launch_dense(const uint16_t *q, const uint16_t *k, const uint16_t *v, float *out, int nseq,
                         int hkv, int G, int dtype, int64_t seq_stride, int max_ctx, const int32_t *ctx,
                         float scale, float *part, int max_splits, hipStream_t s);

@@ -1,0 +1,54 @@
+"""Decode parity where the split plan, the scoring grid and the combine change
+form: more pairs or windows than the plan holds in registers, one to three
+windows (fused and two-kernel combine), 17 of them, selections of a few blocks,
+every block size with all channels kept, and update buffers of 1 to 31
+tokens.  Scores and selections bit for bit, outputs against the fp64 oracle
+within the bound of the parity tests."""
+import numpy as np
+import pytest
+import torch
+
+from _parity import assert_close, gpu_cache, gpu_scores_sel, oracle_decode_all, oracle_pairs, params_pair, scale_of
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+MANY = tuple(70 + 37 * (i % 9) for i in range(33))              # 132 pairs of 4 kv heads
+CASES = {
+    "many_pairs": (dict(ctx=MANY, hkv=4), {}),
+    "at_128_pairs": (dict(ctx=MANY[:32], hkv=4, group=8), {}),
+    "windows_1": (dict(ctx=(1000, 500), hkv=2, rot_window=4096), {}),
+    "windows_2": (dict(ctx=(1000, 500), hkv=2, rot_window=640), {}),
+    "windows_3": (dict(ctx=(1300, 500), hkv=2, rot_window=512), {}),
+    "windows_16": (dict(ctx=(1000, 70), hkv=2, rot_window=64), dict(select=(1, 3))),
+    "windows_17": (dict(ctx=(1080, 70), hkv=2, rot_window=64), dict(select=(1, 3))),
+    "buffers": (dict(ctx=(1, 31, 33, 63, 65, 95, 97, 127), hkv=1, group=7, dtype="bf16"), {}),
+    "few_blocks_b16": (dict(ctx=(9000, 129), hkv=1), dict(force_default=True, default=(32, 1, 16))),
+    "all_selected_b4": (dict(ctx=(4000, 33), hkv=1), dict(force_default=True, default=(16, 2, 4), select=(1, 1))),
+    "quest_b8": (dict(ctx=(3000, 801, 40), hkv=2, rotate=False), dict(force_default=True, default=(128, 1, 8))),
+    "quest_b4_g8": (dict(ctx=(3000, 801, 40), hkv=1, group=8, dtype="bf16", rotate=False),
+                    dict(force_default=True, default=(128, 1, 4), select=(1, 2))),
+    "quest_b16_rotated": (dict(ctx=(5000, 64), hkv=1, dtype="bf16"), dict(force_default=True, default=(128, 1, 16))),
+    "some_keep_all": (dict(ctx=(1500, 900), hkv=2), dict(keep_cand=(16, 64, 128), default=(128, 1, 8), tau_channel=0.01)),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_decode_plan(name):
+    over, extra = CASES[name]
+    spec = gen.spec("c1", **over)
+    cap = spec.max_ctx + 4
+    lay = gen.make_layer(spec, 0, capacity=cap)
+    lp, op = params_pair(spec, **extra)
+    ops = oracle_pairs(op, spec, lay, cap)
+    c = gpu_cache(lp, spec, lay, cap)
+    q = gen.make_queries(spec, 0)
+    out = c.decode(q.cuda(), scale_of())
+    torch.cuda.synchronize()
+    want, sels, scores = oracle_decode_all(ops, spec, q, scale_of())
+    for p in range(spec.num_seqs * spec.hkv):
+        nb = ops[p].info().nblk
+        gs, gsel, _ = gpu_scores_sel(c, p, nb)
+        assert np.array_equal(gs.view(np.uint32), scores[p].view(np.uint32)), f"{name} pair {p}: block scores"
+        assert np.array_equal(gsel, sels[p]), f"{name} pair {p}: selected blocks"
+    assert_close(out.cpu().numpy(), want, name)
