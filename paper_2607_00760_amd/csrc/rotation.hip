@@ -141,16 +141,38 @@ __device__ __forceinline__ float block_sum_jt(float x, float *red) {
     return t;
 }
 
-// grid (windows, pairs * 2); dynamic LDS: A and V [D][JP] floats
+// the rotation that clears A[p][q] (p < q)
+__device__ __forceinline__ void jacobi_params(const float *A, int p, int q, float2 &cs) {
+    const float app = A[p * JP + p], aqq = A[q * JP + q], apq = A[p * JP + q];
+    float c = 1.0f, s = 0.0f;
+    if (apq != 0.0f) {
+        const float tau = (aqq - app) / (2.0f * apq);
+        const float at = fabsf(tau);
+        const float t = (at > 1e15f) ? 0.5f / tau : copysignf(1.0f, tau) / (at + sqrtf(fmaf(tau, tau, 1.0f)));
+        c = 1.0f / sqrtf(fmaf(t, t, 1.0f));
+        s = t * c;
+    }
+    cs = make_float2(c, s);
+}
+
+// grid (windows, pairs * 2); dynamic LDS: A and V [D][JP] floats.  One matrix
+// per compute unit, bound by LDS and vector-ALU time of its 127 steps a sweep:
+// a lane keeps its column pair's indices and rotation in registers, a wave its
+// row pairs' in scalar ones, and the next step's rotations (a chain of
+// divisions and square roots) are computed while V takes this step's.  64
+// matrices: 2.98 ms with indices and rotations read from LDS per block, 2.79
+// now, bit for bit the same.  (All of a thread's loads before its first store
+// measured no faster.)
 __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int W, int nw, int nslices,
                                                 const float *part, float *rot_k, float *rot_v, float *ev_k,
                                                 float *ev_v) {
     extern __shared__ __align__(16) float jsm[];
     float *A = jsm, *V = jsm + D * JP;
-    __shared__ float rc[64], rs[64], red[JT / 64];
-    __shared__ int rp[64], rq[64];
+    __shared__ float2 rcs[2][64];                          // (cos, sin) of the step's 64 rotations, steps in turn
+    __shared__ float red[JT / 64];
     __shared__ int s_done;
     const int w = blockIdx.x, z = blockIdx.y, p = z >> 1, kv = z & 1, tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = ctx[p / hkv];
     const int nwt = (int)min((int64_t)nw, ((int64_t)L + W - 1) / W);     // windows with tokens
     float *R = (kv ? rot_v : rot_k) + ((uint64_t)p * nw + w) * D * D;
@@ -188,50 +210,47 @@ __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int 
         if (tid == 0) s_done = !(off > 1e-12f * dia);
         __syncthreads();
         if (s_done) break;
+        // positions lane and 127 - lane of the tournament: this thread's columns
+        int f = rr_index(lane, 0), g2 = rr_index(D - 1 - lane, 0);
+        if (wave == 0) jacobi_params(A, min(f, g2), max(f, g2), rcs[0][lane]);
+        __syncthreads();
         for (int st = 0; st < D - 1; ++st) {
-            if (tid < 64) {
-                int pp = rr_index(tid, st), qq = rr_index(D - 1 - tid, st);
-                if (pp > qq) { const int t = pp; pp = qq; qq = t; }
-                const float app = A[pp * JP + pp], aqq = A[qq * JP + qq], apq = A[pp * JP + qq];
-                float c = 1.0f, s = 0.0f;
-                if (apq != 0.0f) {
-                    const float tau = (aqq - app) / (2.0f * apq);
-                    const float at = fabsf(tau);
-                    const float t = (at > 1e15f) ? 0.5f / tau : copysignf(1.0f, tau) / (at + sqrtf(fmaf(tau, tau, 1.0f)));
-                    c = 1.0f / sqrtf(fmaf(t, t, 1.0f));
-                    s = t * c;
-                }
-                rp[tid] = pp; rq[tid] = qq; rc[tid] = c; rs[tid] = s;
-            }
-            __syncthreads();
+            const int pm = min(f, g2), qm = max(f, g2);
+            const float2 *cs = rcs[st & 1];
+            const float cm = cs[lane].x, sm = cs[lane].y;
             // A <- J^T A J one 2 x 2 block (rows of pair kk, columns of pair mm)
             // at a time: the block's new value depends on the block only, so
             // one pass suffices (rows first, then columns, per element)
-            for (int u = tid; u < 64 * 64; u += JT) {
-                const int kk = u >> 6, mm = u & 63;
-                const float ck = rc[kk], sk = rs[kk], cm = rc[mm], sm = rs[mm];
-                const int pk = rp[kk], qk = rq[kk], pm = rp[mm], qm = rq[mm];
-                const float bpp = A[pk * JP + pm], bpq = A[pk * JP + qm], bqp = A[qk * JP + pm], bqq = A[qk * JP + qm];
+#pragma unroll
+            for (int j = 0; j < 64 * 64 / JT; ++j) {
+                const int kk = wave + j * (JT / 64);           // wave-uniform: the row pair sits in scalar registers
+                const int fk = rr_index(kk, st), gk = rr_index(D - 1 - kk, st);
+                float *rp = A + min(fk, gk) * JP, *rq = A + max(fk, gk) * JP;
+                const float ck = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cs[kk].x)));
+                const float sk = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cs[kk].y)));
+                const float bpp = rp[pm], bpq = rp[qm], bqp = rq[pm], bqq = rq[qm];
                 const float tpp = ck * bpp - sk * bqp, tpq = ck * bpq - sk * bqq;
                 const float tqp = sk * bpp + ck * bqp, tqq = sk * bpq + ck * bqq;
-                A[pk * JP + pm] = cm * tpp - sm * tpq;
-                A[qk * JP + qm] = sm * tqp + cm * tqq;
-                if (kk == mm) {                            // the rotated pair is zero by construction
-                    A[pk * JP + qm] = 0.0f;
-                    A[qk * JP + pm] = 0.0f;
-                } else {
-                    A[pk * JP + qm] = sm * tpp + cm * tpq;
-                    A[qk * JP + pm] = cm * tqp - sm * tqq;
-                }
+                rp[pm] = cm * tpp - sm * tpq;
+                rq[qm] = sm * tqp + cm * tqq;
+                const bool own = kk == lane;                   // the rotated pair is zero by construction
+                rp[qm] = own ? 0.0f : sm * tpp + cm * tpq;
+                rq[pm] = own ? 0.0f : cm * tqp - sm * tqq;
             }
-            // V <- V J
-            for (int u = tid; u < 64 * D; u += JT) {
-                const int mm = u & 63, i = u >> 6;
-                const float cm = rc[mm], sm = rs[mm];
-                float *vr = V + i * JP;
-                const float x = vr[rp[mm]], y = vr[rq[mm]];
-                vr[rp[mm]] = cm * x - sm * y;
-                vr[rq[mm]] = sm * x + cm * y;
+            __syncthreads();
+            // the next step's columns; its rotations from wave 0 while the
+            // others apply this step's to V (V <- V J)
+            f = lane == 0 ? 0 : (f == D - 1 ? 1 : f + 1);
+            g2 = g2 == D - 1 ? 1 : g2 + 1;
+            if (wave == 0) {
+                if (st + 1 < D - 1) jacobi_params(A, min(f, g2), max(f, g2), rcs[(st + 1) & 1][lane]);
+            } else {
+                for (int i = wave - 1; i < D; i += JT / 64 - 1) {
+                    float *vr = V + i * JP;
+                    const float x = vr[pm], y = vr[qm];
+                    vr[pm] = cm * x - sm * y;
+                    vr[qm] = sm * x + cm * y;
+                }
             }
             __syncthreads();
         }
