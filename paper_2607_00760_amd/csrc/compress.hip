@@ -358,13 +358,29 @@ __device__ __forceinline__ void stage_keys(const float (&yk)[TPW][2], SegSmem<NW
 
 // ------------------------------------------------------------------ kernels
 
-// R^T of K and V and R of V of one rotation into a window slot
-__device__ __forceinline__ void put_rot(float *dst, const float *Rk, const float *Rv) {
-    for (int i = threadIdx.x; i < D * D; i += blockDim.x) {
-        const int j = i / D, c = i % D;        // source R[j][c]
-        dst[c * D + j] = Rk[i];
-        dst[D * D + c * D + j] = Rv[i];
-        dst[2 * D * D + i] = Rv[i];
+// R^T of K and V and R of V of one rotation into a window slot: rows 32 z ..
+// 32 z + 31 of both matrices by one of the RT_SLICES workgroups, through LDS so
+// that reads and transposed writes are whole 128-byte lines (written column by
+// column, 4 bytes at a time, 16 windows took 44 us).
+constexpr int RT_ROWS = 32, RT_SLICES = D / RT_ROWS;
+
+__device__ __forceinline__ void put_rot(float *dst, const float *Rk, const float *Rv, int z) {
+    __shared__ float t[RT_ROWS][D + 1];
+    const int tid = threadIdx.x, j0 = z * RT_ROWS;
+    for (int which = 0; which < 2; ++which) {
+        const float4 *src = (const float4 *)((which ? Rv : Rk) + (uint64_t)j0 * D);
+        for (int i = tid; i < RT_ROWS * D / 4; i += 256) {
+            const float4 x = src[i];
+            float *row = &t[i / (D / 4)][4 * (i % (D / 4))];
+            row[0] = x.x; row[1] = x.y; row[2] = x.z; row[3] = x.w;
+            if (which) ((float4 *)(dst + 2 * D * D + (uint64_t)j0 * D))[i] = x;
+        }
+        __syncthreads();
+        for (int i = tid; i < RT_ROWS * D / 4; i += 256) {      // dst[c][j0 + 4 q ..] = R[j0 + 4 q ..][c]
+            const int c = i / (RT_ROWS / 4), q = 4 * (i % (RT_ROWS / 4));
+            *(float4 *)(dst + which * D * D + c * D + j0 + q) = make_float4(t[q][c], t[q + 1][c], t[q + 2][c], t[q + 3][c]);
+        }
+        __syncthreads();
     }
 }
 
@@ -372,7 +388,8 @@ __device__ __forceinline__ void put_rot(float *dst, const float *Rk, const float
 // (slots past them take the last one: windows that close later get their own)
 __global__ void k_copy_rot(Geom g, const float *rk, const float *rv, int nw_src) {
     const int p = blockIdx.y, w = blockIdx.x, ws = min(w, nw_src - 1);
-    put_rot(g.rot_of(p, w), rk + ((uint64_t)p * nw_src + ws) * D * D, rv + ((uint64_t)p * nw_src + ws) * D * D);
+    put_rot(g.rot_of(p, w), rk + ((uint64_t)p * nw_src + ws) * D * D, rv + ((uint64_t)p * nw_src + ws) * D * D,
+            blockIdx.z);
 }
 
 __global__ void k_set_meta(Geom g, const int32_t *ctx) {
@@ -821,7 +838,7 @@ __global__ void k_close_rot(Geom g, const float *rk, const float *rv) {
     if (pw < 0) return;
     const int w = pw + (int)blockIdx.x;
     if (w >= g.nw) return;
-    put_rot(g.rot_of(p, w), rk + (uint64_t)p * D * D, rv + (uint64_t)p * D * D);
+    put_rot(g.rot_of(p, w), rk + (uint64_t)p * D * D, rv + (uint64_t)p * D * D, blockIdx.z);
 }
 
 __global__ void k_close_done(Geom g) {
@@ -993,7 +1010,7 @@ hipError_t launch_pairs_copy(uint64_t *dst_dev, const uint64_t *src_host, int np
 }
 
 hipError_t launch_copy_rot(const Geom &g, const float *rk, const float *rv, int nw_src, hipStream_t s) {
-    hipLaunchKernelGGL(k_copy_rot, dim3(g.nw, g.npairs), dim3(256), 0, s, g, rk, rv, nw_src);
+    hipLaunchKernelGGL(k_copy_rot, dim3(g.nw, g.npairs, RT_SLICES), dim3(256), 0, s, g, rk, rv, nw_src);
     return hipGetLastError();
 }
 
@@ -1012,7 +1029,7 @@ static hipError_t launch_prefill(const Geom &g, int mode, const uint16_t *k, con
 
 hipError_t launch_close(const Geom &g, const float *rk, const float *rv, const uint16_t *k, const uint16_t *v,
                         int64_t seq_stride, int max_segs, hipStream_t s) {
-    hipLaunchKernelGGL(k_close_rot, dim3(2, g.npairs), dim3(256), 0, s, g, rk, rv);
+    hipLaunchKernelGGL(k_close_rot, dim3(2, g.npairs, RT_SLICES), dim3(256), 0, s, g, rk, rv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (max_segs > 0) {

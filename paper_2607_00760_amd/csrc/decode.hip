@@ -2,9 +2,8 @@
 // Sec. 5.3; stage-2 dynamic sequence compression, Sec. 4.2).
 //
 //   qrot   : q . R_k^T once per (pair, window) -- the rotation is merged into
-//            the single query vector instead of un-rotating the cache.  Each
-//            workgroup produces 16 output channels from an LDS slice of R_k^T;
-//            every output is one fp32 fused chain over the input channels.
+//            the single query vector instead of un-rotating the cache; every
+//            output is one fp32 fused chain over the input channels.
 //   score  : one fp32 score per block key (score.hip).
 //   topk   : exact selection of the k-th largest score key: passes over the
 //            range [min, max] of the keys still in play, 2048 bins each, so
@@ -25,61 +24,46 @@ namespace mosaic {
 namespace {
 
 // ------------------------------------------------------------------ qrot
-// grid (windows * 2, pairs), 256 threads: a workgroup produces 64 output
-// channels j0..j0+63 of every query head of one (pair, window).  It stages the
-// matching 256-byte half of every row of R_k^T (32 KB, each 128-byte line read
-// by one workgroup only) and the pair's queries in LDS; thread (j, h) then runs
-// the fp32 fused chain over the input channels c for head h (and h + 4).
+// grid (windows * 2, pairs), 256 threads: a wave produces 16 output channels of
+// every query head of one (pair, window) as a chain of fp32 matrix products,
+// whose four products each add in ascending k, one rounding per term: bit for
+// bit the fp32 fused chain over the input channels.  R_k^T goes from memory
+// straight into operands, all loads in flight at once: no staging and a third
+// of the code (the kernel's 5 us are those of any short kernel).
 constexpr int QROT_COLS = 64;
 
 __global__ void __launch_bounds__(256) k_qrot(Geom g, WsGeom ws, const uint16_t *q) {
-    __shared__ __align__(16) float rt[D][QROT_COLS];      // R_k^T[c][j0 + jj] = R_k[j0 + jj][c]
-    __shared__ float qs[8][D];
+    __shared__ float qs[8][D + 4];                         // rows 4 banks apart
     constexpr int NCG = D / QROT_COLS;
-    const int w = blockIdx.x / NCG, j0 = (blockIdx.x % NCG) * QROT_COLS;
-    const int p = blockIdx.y, tid = threadIdx.x, G = g.G;
+    const int w = blockIdx.x / NCG, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q4 = lane >> 4;
+    const int j = (blockIdx.x % NCG) * QROT_COLS + 16 * (tid >> 6) + l16;      // this lane's output channel
+    const int p = blockIdx.y, G = g.G;
     if (ws.tkx && blockIdx.x == 0) {        // the multi-workgroup top-k's histograms of this call
         uint32_t *h = ws.tkx + (uint64_t)p * (ws.tkx_stride / 4);
         for (int i = tid; i < 3 * 2048; i += 256) h[i] = 0u;
     }
+    float r[D / 4];                                        // R_k^T[4 i + q4][j]
     if (g.rotated) {
-        const float *src = g.rot_of(p, w);
-        constexpr int PER = D * QROT_COLS / 4 / 256;       // 16-byte pieces per thread
-        uint4 t[PER];
+        const float *src = g.rot_of(p, w) + q4 * D + j;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int idx = tid + 256 * k, c = idx / (QROT_COLS / 4), part = idx % (QROT_COLS / 4);
-            t[k] = *(const uint4 *)(src + c * D + j0 + 4 * part);
-        }
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int idx = tid + 256 * k, c = idx / (QROT_COLS / 4), part = idx % (QROT_COLS / 4);
-            *(uint4 *)&rt[c][4 * part] = t[k];
-        }
+        for (int i = 0; i < D / 4; ++i) r[i] = src[4 * i * D];
     }
-    for (int i = tid; i < G * D; i += 256) qs[i / D][i % D] = h2f(q[(uint64_t)p * G * D + i], g.dtype);
+    for (int i = tid; i < 8 * D; i += 256) qs[i / D][i % D] = i < G * D ? h2f(q[(uint64_t)p * G * D + i], g.dtype) : 0.0f;
     __syncthreads();
-    const int jj = tid & (QROT_COLS - 1), h0 = tid / QROT_COLS;   // heads h0 and h0 + 4
-    float a0 = 0.0f, a1 = 0.0f;
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    f4 acc = f4{0.0f, 0.0f, 0.0f, 0.0f};                   // heads 4 q4 .. 4 q4 + 3 of channel j
     if (g.rotated) {
-        if (h0 + 4 < G) {
-#pragma unroll 8
-            for (int c = 0; c < D; ++c) {
-                const float r = rt[c][jj];
-                a0 = fmaf(qs[h0][c], r, a0);
-                a1 = fmaf(qs[h0 + 4][c], r, a1);
-            }
-        } else if (h0 < G) {
-#pragma unroll 8
-            for (int c = 0; c < D; ++c) a0 = fmaf(qs[h0][c], rt[c][jj], a0);
+        const float *qh = &qs[l16 & 7][q4];
+#pragma unroll
+        for (int i = 0; i < D / 4; ++i) {
+            const float a = l16 < 8 ? qh[4 * i] : 0.0f;
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, r[i], acc, 0, 0, 0);
         }
     } else {
-        a0 = (h0 < G) ? qs[h0][j0 + jj] : 0.0f;
-        a1 = (h0 + 4 < G) ? qs[h0 + 4][j0 + jj] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = qs[(4 * q4 + e) & 7][j];
     }
-    float *dst = ws.qrot + (uint64_t)p * (ws.qrot_stride / 4) + ((uint64_t)w * D + j0 + jj) * g.GP;
-    if (h0 < g.GP) dst[h0] = (h0 < G) ? a0 : 0.0f;
-    if (h0 + 4 < g.GP) dst[h0 + 4] = (h0 + 4 < G) ? a1 : 0.0f;
+    if (4 * q4 < g.GP) *(f4 *)(ws.qrot + (uint64_t)p * (ws.qrot_stride / 4) + ((uint64_t)w * D + j) * g.GP + 4 * q4) = acc;
 }
 
 // ------------------------------------------------------------------ topk
