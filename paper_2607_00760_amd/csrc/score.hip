@@ -5,7 +5,7 @@
 // in ascending order (v_ffbl on the current word), fp32 fused chain over the
 // kept channels, max over the GQA group.  These scores decide the selection,
 // so their arithmetic order is fixed.
-#include "decode_common.h"
+#include "topk.h"
 
 namespace mosaic {
 
@@ -279,6 +279,129 @@ __global__ void __launch_bounds__(256) k_score(Geom g, WsGeom ws, int spw) {
     }
 }
 
+// ------------------------------------------------------------------ short contexts
+// grid (pairs): query rotation, scores and selection of a pair of one rotation
+// window and at most FRONT_BLOCKS blocks, by one workgroup.  As kernels of
+// their own the three take 5 us each before their work counts (launch, code
+// fetch, the round trip through memory); here the scores stay in LDS for the
+// selection.  What the attention and a caller's inspection read is written as
+// the separate kernels write it.  1 x 4117 tokens, 8 kv heads: 4.9 + 8.2 + 8.6
+// us apart, 18.0 together (8 requests of 1000 tokens: 20 and 13.8); beyond FRONT_BLOCKS a pair's keys are worth
+// more than one compute unit.
+constexpr int FRONT_SEGS = FRONT_BLOCKS / 4 + 2;
+
+struct TopkLds {
+    const float *sc;
+    const uint8_t *bz;
+    const uint2 *bi;
+    __device__ __forceinline__ float4 score4(int i) const { return *(const float4 *)(sc + i); }
+    __device__ __forceinline__ uint32_t size4(int i) const { return *(const uint32_t *)(bz + i); }
+    __device__ __forceinline__ uint2 info(int i) const { return bi[i]; }
+};
+
+template <int DT, int GP>
+__global__ void __launch_bounds__(1024) k_front(Geom g, WsGeom ws, const uint16_t *q) {
+    __shared__ float qraw[8][D + 4];
+    __shared__ __align__(16) float qs[D * GP];
+    __shared__ Desc ds[FRONT_SEGS];
+    __shared__ uint16_t b2s[FRONT_BLOCKS];                   // block -> segment
+    __shared__ __align__(16) float ssc[FRONT_BLOCKS];
+    __shared__ __align__(16) uint8_t sbz[FRONT_BLOCKS];
+    __shared__ uint2 sbi[FRONT_BLOCKS];
+    __shared__ TopkSmem sm;
+    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q4 = lane >> 4, G = g.G;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // R_k^T[4 i + q4][j] for the rotation's eight waves (16 output channels each)
+    float r[D / 4];
+    const int j = 16 * wave + l16;
+    const bool rot = g.rotated && wave < D / 16;
+    if (rot) {
+        const float *src = g.rot_of(p, 0) + q4 * D + j;
+#pragma unroll
+        for (int i = 0; i < D / 4; ++i) r[i] = src[4 * i * D];
+    }
+    const PairMeta meta = *g.meta_of(p);
+    if (tid < 8 * D) qraw[tid / D][tid % D] = tid < G * D ? h2f(q[(uint64_t)p * G * D + tid], g.dtype) : 0.0f;
+    int nf, prov, nbuf;
+    const int ndesc = pair_ndesc(meta, nf, prov, nbuf);
+    if (tid < ndesc) {
+        const Desc d = g.desc_of(p)[tid];
+        ds[tid] = d;
+        const int nb = ((d.flags & 1) ? UBUF : SEG) >> d.log2b;
+        for (int x = 0; x < nb; ++x) b2s[min((int)d.first_block + x, FRONT_BLOCKS - 1)] = (uint16_t)tid;
+    }
+    __syncthreads();
+    const int nblk = ndesc > 0 ? min((int)ds[ndesc - 1].first_block +
+                                     (((ds[ndesc - 1].flags & 1) ? UBUF : SEG) >> ds[ndesc - 1].log2b), FRONT_BLOCKS) : 0;
+    if (wave < D / 16) {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        f4 acc = f4{0.0f, 0.0f, 0.0f, 0.0f};                 // heads 4 q4 .. 4 q4 + 3 of channel j
+        if (rot) {                                           // (the fp32 fused chain, as in the rotation kernel)
+            const float *qh = &qraw[l16 & 7][q4];
+#pragma unroll
+            for (int i = 0; i < D / 4; ++i)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(l16 < 8 ? qh[4 * i] : 0.0f, r[i], acc, 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = qraw[(4 * q4 + e) & 7][j];
+        }
+        if (4 * q4 < GP) {
+            *(f4 *)&qs[j * GP + 4 * q4] = acc;
+            *(f4 *)(ws.qrot + (uint64_t)p * (ws.qrot_stride / 4) + (uint64_t)j * GP + 4 * q4) = acc;
+        }
+    }
+    __syncthreads();
+    float *out = ws.score + (uint64_t)p * (ws.score_stride / 4);
+    uint2 *binfo = ws.binfo + (uint64_t)p * (ws.binfo_stride / 8);
+    uint8_t *bsize = ws.bsize + (uint64_t)p * ws.bsize_stride;
+    const uint8_t *sc = g.sc_of(p);
+    for (int b0 = 0; b0 < nblk; b0 += 1024) {
+        const int b = b0 + tid;
+        const bool valid = b < nblk;
+        if (__ballot(valid) == 0ull) break;                  // (wave-uniform; no barrier inside the loop)
+        const Desc d = ds[valid ? b2s[b] : 0];
+        const int x0 = b - (int)d.first_block;
+        const int rk = valid ? d.r : 0, l2g = d.log2g;
+        const uint8_t *rec = valid ? sc + d.sc_off + (uint32_t)x0 * (uint32_t)vec_bytes(rk, l2g, g.trunc) : sc;
+        const bool a16 = __all(!valid || (l2g == 0 && ((uintptr_t)rec & 15u) == 0 && g.trunc == D));
+        PVec<48> x;
+        load_pvec<48, -1, true>(x, rec, rec + bm_bytes(l2g, g.trunc), wave_max_i(rk), a16);
+        if (g.trunc < D) mask_words(x.bw, g.trunc >> l2g);
+        float acc[GP];
+#pragma unroll
+        for (int h = 0; h < GP; ++h) acc[h] = 0.0f;
+        score_any<DT, GP, 48, true>(x, rk, l2g, lds_addr(qs), acc);
+        float best = acc[0];
+#pragma unroll
+        for (int h = 1; h < GP; ++h)
+            if (h < G) best = fmaxf(best, acc[h]);
+        if (__float_as_uint(best) == 0x80000000u) best = 0.0f;
+        if (valid) {
+            const uint2 info = blk_info(d.tok_off + (uint32_t)(x0 << d.log2b) *
+                                        (uint32_t)(2 * tok_vec_bytes(d.r, d.log2g, g.trunc, g.fp8)), d.r, d.log2g, d.log2b);
+            out[b] = best; ssc[b] = best;
+            binfo[b] = info; sbi[b] = info;
+            bsize[b] = d.log2b; sbz[b] = d.log2b;
+        }
+    }
+    __syncthreads();
+    const int budget = pair_budget(g, nblk, nf, prov);
+    auto on = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        if (threadIdx.x >= 64 * NW) return;                 // (an ended wave counts at no barrier)
+        topk_reg<4, NW>(g, ws, TopkLds{ssc, sbz, sbi}, p, nblk, ndesc, budget, sm);
+    };
+    if (nblk <= 256) on(IntC<1>{});
+    else if (nblk <= 1024) on(IntC<4>{});
+    else on(IntC<16>{});
+}
+
+template <int DT, int GP>
+hipError_t front_dt(const Geom &g, const WsGeom &w, const uint16_t *q, hipStream_t s) {
+    hipLaunchKernelGGL((k_front<DT, GP>), dim3(g.npairs), dim3(1024), 0, s, g, w, q);
+    return hipGetLastError();
+}
+
 template <int DT, int GP>
 hipError_t score_dt(const Geom &g, const WsGeom &w, int max_desc_used, bool fixed, bool small, hipStream_t s) {
     // as many segments per workgroup as leave about 1024 workgroups (the chip
@@ -296,6 +419,11 @@ hipError_t score_dt(const Geom &g, const WsGeom &w, int max_desc_used, bool fixe
 }
 
 }  // namespace
+
+hipError_t launch_front(const Geom &g, const WsGeom &w, const uint16_t *q, hipStream_t s) {
+    if (g.dtype) return g.GP == 4 ? front_dt<1, 4>(g, w, q, s) : front_dt<1, 8>(g, w, q, s);
+    return g.GP == 4 ? front_dt<0, 4>(g, w, q, s) : front_dt<0, 8>(g, w, q, s);
+}
 
 hipError_t launch_score(const Geom &g, const WsGeom &w, int max_desc_used, bool fixed, bool small, hipStream_t s) {
     if (g.dtype) return g.GP == 4 ? score_dt<1, 4>(g, w, max_desc_used, fixed, small, s) : score_dt<1, 8>(g, w, max_desc_used, fixed, small, s);
