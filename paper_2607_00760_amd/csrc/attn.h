@@ -202,7 +202,13 @@ __device__ __forceinline__ int plan_small(const Geom &g, const WsGeom &ws, int g
     const float tokens = (float)st * UBUF * g.sel_num / g.sel_den;
     const int b128 = (int)(128.0f * (float)kt / fmaxf(tokens, 1.0f) + 0.5f);
     const int fit = (int)(((long long)nmax * SPLIT_MIN + ws.max_sel - 1) / ws.max_sel);
-    const int bps = min(max(max((kt + avail - 1) / avail, fit), min(max(b128, SPLIT_LEAST), SPLIT_MIN)), SPLIT_MAX);
+    // more than SPLIT_MAX blocks for each resident workgroup: as many whole
+    // rounds as that takes, of equal splits (a last round of a few splits
+    // costs as much as a full one: a million tokens, 1037 splits of 128 blocks
+    // for 1024 workgroups, 84 us; two rounds of 60 blocks, 72 us)
+    const int rounds = (kt + avail * SPLIT_MAX - 1) / (avail * SPLIT_MAX);
+    const int room = rounds > 1 ? rounds * ws.split_slots - min(et, ws.split_slots) : avail;
+    const int bps = min(max(max((kt + room - 1) / room, fit), min(max(b128, SPLIT_LEAST), SPLIT_MIN)), SPLIT_MAX);
     const uint32_t inv = 0xffffffffu / (uint32_t)bps + 1u;      // x / bps = umulhi(x, inv) for x * bps < 2^32
     auto splits = [&](int c) { return (int)__umulhi((uint32_t)(c + bps - 1), inv); };
     int ns = nbuf > 0 ? 1 : 0;
@@ -877,13 +883,15 @@ k_attn(Geom g, WsGeom ws, float scale, const uint16_t *qraw) {
 
 template <int DT, int GP>
 hipError_t attn_dt(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s) {
-    // the plan has at most max(slots, selected blocks / SPLIT_MAX) splits
-    // of whole blocks plus one rounding split per window and per buffer,
+    // the plan has at most as many splits of whole blocks as fill its rounds
+    // (rounds - 1 of them hold SPLIT_MAX blocks for each workgroup) plus one rounding split per window and per buffer,
     // and never more than every pair's whole partial array or the most blocks
     // that can be selected in splits of SPLIT_LEAST
     const size_t smem = ATTN_HDR_BYTES + (size_t)ATTN_NWV * TILE_BYTES;
     const long long extra = (long long)g.npairs * (g.nw + 1);
-    const long long whole = std::max<long long>(w.split_slots, (long long)g.npairs * ceil_div(w.max_sel, SPLIT_MAX));
+    const long long room = std::max<long long>(w.split_slots - extra, w.split_slots / 4);    // (the plan's, at least)
+    const long long most = (long long)g.npairs * ceil_div(w.max_sel, SPLIT_MAX);
+    const long long whole = w.split_slots + (most > room ? most * w.split_slots / std::max<long long>(room, 1) : 0);
     const long long least = (long long)g.npairs * ceil_div(w.max_sel, SPLIT_LEAST);
     const long long nwg = std::min<long long>(std::min(whole, least) + extra, (long long)g.npairs * w.max_splits);
     auto go = [&](auto kernel) {
