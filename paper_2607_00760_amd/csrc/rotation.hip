@@ -158,11 +158,12 @@ __device__ __forceinline__ void jacobi_params(const float *A, int p, int q, floa
 // grid (windows, pairs * 2); dynamic LDS: A and V [D][JP] floats.  One matrix
 // per compute unit, bound by LDS and vector-ALU time of its 127 steps a sweep:
 // a lane keeps its column pair's indices and rotation in registers, a wave its
-// row pairs' in scalar ones, and the next step's rotations (a chain of
-// divisions and square roots) are computed while V takes this step's.  64
-// matrices: 2.98 ms with indices and rotations read from LDS per block, 2.79
-// now, bit for bit the same.  (All of a thread's loads before its first store
-// measured no faster.)
+// row pairs' in scalar ones; V stays in registers, its columns moving between
+// lanes as the tournament moves them, so only A goes through LDS; and the next
+// step's rotations (a chain of divisions and square roots) are computed while
+// V takes this step's.  64 matrices: 2.98 ms with everything in LDS, 2.69 with
+// the indices and rotations in registers, 2.35 now, bit for bit the same.  (All of a thread's loads of
+// A before its first store measured no faster.)
 __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int W, int nw, int nslices,
                                                 const float *part, float *rot_k, float *rot_v, float *ev_k,
                                                 float *ev_v) {
@@ -193,7 +194,16 @@ __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int 
         float x = 0.0f;
         for (int sl = 0; sl < nslices; ++sl) x += src[(uint64_t)sl * D * D + u];
         A[r * JP + c] = x;
-        V[(i / D) * JP + i % D] = (i / D == i % D) ? 1.0f : 0.0f;
+    }
+    // positions lane and 127 - lane of the tournament: this thread's columns;
+    // V's rows VR wave .. in registers, the columns at the lane's positions
+    constexpr int VR = D / (JT / 64);
+    int f = rr_index(lane, 0), g2 = rr_index(D - 1 - lane, 0);
+    float vf[VR], vs[VR];
+#pragma unroll
+    for (int i = 0; i < VR; ++i) {
+        vf[i] = f == VR * wave + i ? 1.0f : 0.0f;
+        vs[i] = g2 == VR * wave + i ? 1.0f : 0.0f;
     }
     __syncthreads();
     for (int sweep = 0; sweep < JACOBI_MAX_SWEEPS; ++sweep) {
@@ -210,14 +220,26 @@ __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int 
         if (tid == 0) s_done = !(off > 1e-12f * dia);
         __syncthreads();
         if (s_done) break;
-        // positions lane and 127 - lane of the tournament: this thread's columns
-        int f = rr_index(lane, 0), g2 = rr_index(D - 1 - lane, 0);
         if (wave == 0) jacobi_params(A, min(f, g2), max(f, g2), rcs[0][lane]);
         __syncthreads();
         for (int st = 0; st < D - 1; ++st) {
             const int pm = min(f, g2), qm = max(f, g2);
             const float2 *cs = rcs[st & 1];
             const float cm = cs[lane].x, sm = cs[lane].y;
+            // V <- V J, then the tournament's move of its columns: first
+            // positions take their right neighbour's, second ones their left
+            // neighbour's (position 0 stays, 127 takes position 1's)
+            auto turn_v = [&] {
+                const float sv = f < g2 ? sm : -sm;            // the first position may hold the larger index
+#pragma unroll
+                for (int i = 0; i < VR; ++i) {
+                    const float x = cm * vf[i] - sv * vs[i], y = sv * vf[i] + cm * vs[i];
+                    const float t = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(y), __float_as_int(x), 0x130, 0xf, 0xf, false));
+                    vs[i] = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(t), __float_as_int(y), 0x138, 0xf, 0xf, false));
+                    vf[i] = lane == 0 ? x : t;
+                }
+            };
+            if (wave == 0) turn_v();                           // (the other waves while wave 0 is at the rotations)
             // A <- J^T A J one 2 x 2 block (rows of pair kk, columns of pair mm)
             // at a time: the block's new value depends on the block only, so
             // one pass suffices (rows first, then columns, per element)
@@ -238,23 +260,21 @@ __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int 
                 rq[pm] = own ? 0.0f : cm * tqp - sm * tqq;
             }
             __syncthreads();
-            // the next step's columns; its rotations from wave 0 while the
-            // others apply this step's to V (V <- V J)
+            // the next step's rotations from wave 0 while the others apply this step's to V
+            if (wave != 0) turn_v();
             f = lane == 0 ? 0 : (f == D - 1 ? 1 : f + 1);
             g2 = g2 == D - 1 ? 1 : g2 + 1;
-            if (wave == 0) {
-                if (st + 1 < D - 1) jacobi_params(A, min(f, g2), max(f, g2), rcs[(st + 1) & 1][lane]);
-            } else {
-                for (int i = wave - 1; i < D; i += JT / 64 - 1) {
-                    float *vr = V + i * JP;
-                    const float x = vr[pm], y = vr[qm];
-                    vr[pm] = cm * x - sm * y;
-                    vr[qm] = sm * x + cm * y;
-                }
-            }
+            if (wave == 0 && st + 1 < D - 1) jacobi_params(A, min(f, g2), max(f, g2), rcs[(st + 1) & 1][lane]);
             __syncthreads();
         }
     }
+    // V's columns are back at their first positions (127 moves of 127 places)
+#pragma unroll
+    for (int i = 0; i < VR; ++i) {
+        V[(VR * wave + i) * JP + rr_index(lane, 0)] = vf[i];
+        V[(VR * wave + i) * JP + rr_index(D - 1 - lane, 0)] = vs[i];
+    }
+    __syncthreads();
     // rank the eigenvalues (descending, index ascending on ties); eigenvector
     // i is column i of V
     if (tid < D) {
