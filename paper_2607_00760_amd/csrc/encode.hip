@@ -21,11 +21,13 @@
 // 33 K cycles of a wave (fp32 products run at twice the rate of plain fp32
 // FMAs, but a wave's products and another wave's vector instructions were
 // measured not to overlap: 225 + 262 us apart, 487 us together), the ranking
-// and packing 16 K (first candidate passes) to 50 K.  Two waves per SIMD (256
-// registers) hide most of the loads and barriers.
+// and packing 14 K (first candidate passes) to 38 K, and the two make up 98 %
+// of the time.  Two waves per SIMD (256 registers) hide the loads and barriers;
+// spilled registers cost far more than their instructions say (110 of them 40 %
+// of the forced strategy's time), hence the ordering constraints below.
 // 2 x 131072 tokens, 8 kv heads, bf16: ranks counted through LDS, lane per
-// channel, took 16.8 ms; this kernel takes 3.05 ms.  4 x 32785 tokens in fp16,
-// first candidate: 6.87 ms and 1.02 ms.
+// channel, took 16.8 ms; this kernel takes 2.09 ms.  4 x 32785 tokens in fp16,
+// first candidate: 6.87 ms and 0.88 ms.
 #include <utility>
 
 #include "mosaic_internal.h"
@@ -47,7 +49,7 @@ struct EncSmem {
     float yb[SEG * YB_STRIDE];
     float mean[MEAN_ROWS * MEAN_STRIDE];
     uint8_t vst[SEG * ST_MAX];            // the staged records of the values
-    uint32_t pass[9][2];                  // per candidate: passes for K, for V
+    uint32_t pass[12][2];                 // per exchange: candidates that pass for K, for V
     int log2b;
 };
 static_assert(sizeof(float) * SEG * YB_STRIDE >= SEG * ST_MAX, "the keys' staged records fit their channels' place");
@@ -272,6 +274,48 @@ struct Cuts {
     int t[3], nx[3];
 };
 
+// The cuts of 16 and 32 kept single channels: the 32 largest so far stay
+// sorted and the last 32 only meet the list, since the 16th and 17th of a
+// bitonic 32 are a half-cleaner away (2150 vector instructions; with the 48
+// largest below, 2800).
+__device__ __forceinline__ Cuts cuts32(const float (&y)[D], const Trunc &tr) {
+    Cuts c;
+    int l[32], rest = -1;
+    load_keys<1, 0, 32>(y, tr, l, 0);
+    oe_sort<0, 31>(l);
+    auto meet = [&](auto first) {                            // l: the 32 largest of it and 32 more, bitonic
+        int n[32];
+        load_keys<1, decltype(first)::value, 32>(y, tr, n, 0);
+        oe_sort<0, 31>(n);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            rest = max(rest, min(l[i], n[31 - i]));
+            l[i] = max(l[i], n[31 - i]);
+            asm volatile("" : "+v"(rest), "+v"(l[i]));         // (in this order: both inputs end here)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    meet(std::integral_constant<int, 32>{});
+    bitonic_desc<0, 32>(l);
+    __builtin_amdgcn_sched_barrier(0);
+    meet(std::integral_constant<int, 64>{});
+    bitonic_desc<0, 32>(l);
+    __builtin_amdgcn_sched_barrier(0);
+    meet(std::integral_constant<int, 96>{});
+    int t16 = 0x7fffffff, n16 = -1, t32 = 0x7fffffff;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int hi = max(l[i], l[16 + i]), lo = min(l[i], l[16 + i]);
+        t16 = min(t16, hi);
+        n16 = max(n16, lo);
+        t32 = min(t32, lo);
+    }
+    c.t[0] = t16; c.nx[0] = n16; c.t[1] = t32; c.nx[1] = rest; c.t[2] = 0; c.nx[2] = -1;
+    return c;
+}
+
 template <int G>
 __device__ __forceinline__ Cuts cuts_of(const float (&y)[D], const Trunc &tr) {
     Cuts c;
@@ -387,6 +431,35 @@ __device__ __forceinline__ float dropped(const float (&y)[D], const Trunc &tr, i
         return kept ? 0.0f : e;
     };
     return leaf_tree<0, D / G>(leaf);
+}
+
+// the same for 16 and 32 kept at once (cuts t16, t32, no ties): squares, sums
+// and scores are shared
+template <int G>
+__device__ __forceinline__ void dropped_pair(const float (&y)[D], const Trunc &tr, int t16, int t32, float &d16, float &d32) {
+    struct Two { float a, b; };
+    auto leaf = [&](auto i) {
+        constexpr int I = decltype(i)::value;
+        bound_ahead<I, 8 / G>();
+        auto e = [&](int j) { const float x = y[G * I + j]; return x * x; };
+        float s;
+        if constexpr (G == 1) s = e(0);
+        else if constexpr (G == 2) s = e(0) + e(1);
+        else s = (e(0) + e(1)) + (e(2) + e(3));
+        const int k = group_key<G, I>(y, tr);
+        return Two{below_cut(s, k, t16), below_cut(s, k, t32)};
+    };
+    auto tree = [&](auto self, auto first, auto n) -> Two {
+        constexpr int B = decltype(first)::value, N = decltype(n)::value;
+        if constexpr (N == 1) return leaf(first);
+        else {
+            const Two a = self(self, first, std::integral_constant<int, N / 2>{});
+            const Two b = self(self, std::integral_constant<int, B + N / 2>{}, std::integral_constant<int, N / 2>{});
+            return Two{a.a + b.a, a.b + b.b};
+        }
+    };
+    const Two t = tree(tree, std::integral_constant<int, 0>{}, std::integral_constant<int, D / G>{});
+    d16 = t.a; d32 = t.b;
 }
 
 // w <- 2 w + (k >= t)
@@ -717,10 +790,20 @@ k_encode(Geom g, const uint16_t *k, const uint16_t *v, int64_t seq_stride, uint8
     int cut = 0;                                            // this token's cut under the chosen strategy
     bool ties = false;
     {
-        // the levels' cuts, by log2 of the group size
+        // the levels' cuts, by log2 of the group size; with a level's cuts come
+        // the dropped energies of its 16 and 32 kept, those of 48 when asked
         int ct[3][3];
-        uint32_t have = 0u, tie_bits = 0u;                  // tie_bits: bits 3 log2g + (r / 16 - 1)
+        uint32_t have = 0u, tie_bits = 0u, pass = 0u;       // pass, tie_bits: bits 3 log2g + (r / 16 - 1)
+        bool have48 = false;                                // the cut of 48 single channels
         int chosen = 0;
+        uint32_t slot = 0u;                                 // the next exchange between the waves
+        auto agree = [&](uint32_t own) {                    // the bits that both waves set
+            if ((threadIdx.x & 63) == 0) sm.pass[slot][which] = own;
+            lds_barrier();
+            const uint32_t both = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sm.pass[slot][0] & sm.pass[slot][1]));
+            ++slot;
+            return both;
+        };
 #pragma unroll
         for (int i = 0; i < 3; ++i) ct[i][0] = ct[i][1] = ct[i][2] = 0;
 #pragma unroll 1
@@ -729,32 +812,48 @@ k_encode(Geom g, const uint16_t *k, const uint16_t *v, int64_t seq_stride, uint8
             if (!known) { r = g.keep_cand[ci / 3]; log2g = enc_log2(g.group_cand[ci % 3]); }
             const int ri = r / 16 - 1;
             chosen = 3 * log2g + ri;
-            if (!((have >> log2g) & 1u)) {
-                auto level = [&](auto gc, int (&t3)[3]) {
-                    const Cuts c = cuts_of<decltype(gc)::value>(y, tr);
+            const bool full = log2g == 0 && ri == 2 && !have48;
+            if (!((have >> log2g) & 1u) || full) {
+                auto level = [&](const Cuts &c, int (&t3)[3]) {
 #pragma unroll
                     for (int i = 0; i < 3; ++i) {
                         t3[i] = c.t[i];
                         if (__ballot(c.t[i] == c.nx[i])) tie_bits |= 1u << (3 * log2g + i);
                     }
                 };
-                if (log2g == 0) level(std::integral_constant<int, 1>{}, ct[0]);
-                else if (log2g == 1) level(std::integral_constant<int, 2>{}, ct[1]);
-                else level(std::integral_constant<int, 4>{}, ct[2]);
+                if (full) { level(cuts_of<1>(y, tr), ct[0]); have48 = true; }
+                else if (log2g == 0) level(cuts32(y, tr), ct[0]);
+                else if (log2g == 1) level(cuts_of<2>(y, tr), ct[1]);
+                else level(cuts_of<4>(y, tr), ct[2]);
+                if (!known && !((have >> log2g) & 1u)) {
+                    renew(y);
+                    float d16, d32;
+                    auto both = [&](auto gc, const int (&t3)[3]) {
+                        constexpr int G = decltype(gc)::value;
+                        if ((tie_bits >> (3 * log2g)) & 3u) {
+                            d16 = dropped<G>(y, tr, 16, t3[0], true);
+                            d32 = dropped<G>(y, tr, 32, t3[1], true);
+                        } else dropped_pair<G>(y, tr, t3[0], t3[1], d16, d32);
+                    };
+                    if (log2g == 0) both(std::integral_constant<int, 1>{}, ct[0]);
+                    else if (log2g == 1) both(std::integral_constant<int, 2>{}, ct[1]);
+                    else both(std::integral_constant<int, 4>{}, ct[2]);
+                    pass |= agree((tree64(d16) < lim ? 1u : 0u) | (tree64(d32) < lim ? 2u : 0u)) << (3 * log2g);
+                }
                 have |= 1u << log2g;
             }
             if (known || ci == 8) break;                    // the last candidate needs no test
-            renew(y);
-            const bool tie = (tie_bits >> chosen) & 1u;
-            auto at = [&](const int (&t3)[3]) { return ri == 0 ? t3[0] : ri == 1 ? t3[1] : t3[2]; };
-            float d;
-            if (log2g == 0) d = dropped<1>(y, tr, r, at(ct[0]), tie);
-            else if (log2g == 1) d = dropped<2>(y, tr, r, at(ct[1]), tie);
-            else d = dropped<4>(y, tr, r, at(ct[2]), tie);
-            d = tree64(d);
-            if ((threadIdx.x & 63) == 0) sm.pass[ci][which] = d < lim ? 1u : 0u;
-            lds_barrier();
-            if (__builtin_amdgcn_readfirstlane((int)(sm.pass[ci][0] & sm.pass[ci][1]))) break;
+            if (ri == 2) {
+                renew(y);
+                const bool tie = (tie_bits >> chosen) & 1u;
+                float d;
+                if (log2g == 0) d = dropped<1>(y, tr, 48, ct[0][2], tie);
+                else if (log2g == 1) d = dropped<2>(y, tr, 48, ct[1][2], tie);
+                else d = dropped<4>(y, tr, 48, ct[2][2], tie);
+                if (agree(tree64(d) < lim ? 1u : 0u)) break;
+            } else if ((pass >> chosen) & 1u) {
+                break;
+            }
         }
 #pragma unroll
         for (int i = 0; i < 9; ++i) cut = chosen == i ? ct[i / 3][i % 3] : cut;
