@@ -48,6 +48,7 @@ int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 struct mosaic_cache {
     mosaic_params P;
     int num_seqs, max_tokens, rotated, npairs, GP, nw, max_desc, max_blocks, max_sel, max_splits;
+    int split_min;               // blocks of the smallest split that max_splits has room for
     int maxrec, minb;
     uint32_t slot_tok, slot_sc;  // single-pass compression: worst-case bytes of a segment's records
     mosaic_layout lay;
@@ -109,6 +110,7 @@ struct mosaic_cache {
         w.wres = (float *)(b + wsl.wres_off); w.wres_stride = wsl.wres_stride;
         w.tkx = wsl.tkx_stride ? (uint32_t *)(b + wsl.tkx_off) : nullptr; w.tkx_stride = wsl.tkx_stride;
         w.max_blocks = max_blocks; w.max_splits = max_splits; w.max_sel = max_sel;
+        w.split_min = split_min;
         return w;
     }
 };
@@ -275,7 +277,6 @@ static mosaic_status cache_create(const mosaic_params *params, int32_t num_seqs,
     const int64_t max_budget = ((int64_t)c->max_desc * SEG * params->select_num + params->select_den - 1) /
                                params->select_den;
     c->max_sel = (int)std::min<int64_t>(c->max_blocks, (max_budget + minb - 1) / minb + 1);
-    c->max_splits = (c->max_sel + SPLIT_MIN - 1) / SPLIT_MIN + c->nw + 1;
     // arena layout
     mosaic_layout &l = c->lay;
     std::memset(&l, 0, sizeof(l));
@@ -324,34 +325,42 @@ static mosaic_status cache_create(const mosaic_params *params, int32_t num_seqs,
     off = align256(off + (uint64_t)num_seqs * 4);
     l.total = off;
     l.num_pairs = c->npairs; l.max_desc = c->max_desc; l.num_windows = c->nw;
-    // decode workspace layout
+    // decode workspace layout.  Split partials are sized for splits of at least
+    // split_min blocks: SPLIT_MIN, or SPLIT_FINE where the selections cannot
+    // fill the chip with splits of SPLIT_MIN and the workspace stays well
+    // inside the fixed buffer of the no-allocation entry point.
     mosaic_ws_layout &w = c->wsl;
-    std::memset(&w, 0, sizeof(w));
-    off = 0;
-    auto wregion = [&](uint64_t &o, uint64_t &stride, uint64_t per_pair) {
-        stride = align256(per_pair);
-        o = off;
-        off = align256(off + stride * (uint64_t)c->npairs);
-    };
-    wregion(w.qrot_off, w.qrot_stride, (uint64_t)c->nw * D * c->GP * 4);
-    wregion(w.score_off, w.score_stride, (uint64_t)c->max_blocks * 4);
-    wregion(w.sel_off, w.sel_stride, (uint64_t)c->max_blocks * 4);
-    // wsel: window starts in the selected list, k, block count (pair 0: and
-    // the call's blocks per split)
-    wregion(w.wsel_off, w.wsel_stride, (uint64_t)(c->nw + 3) * 4);
-    // part: split partials (max, sum, unrotated accumulator per head)
-    wregion(w.part_off, w.part_stride, (uint64_t)c->max_splits * c->GP * (D + 2) * 4);
-    wregion(w.tag_off, w.tag_stride, (uint64_t)c->max_splits * 4);
-    wregion(w.binfo_off, w.binfo_stride, (uint64_t)c->max_blocks * 8);
-    wregion(w.bsize_off, w.bsize_stride, (uint64_t)c->max_blocks);
-    wregion(w.selinfo_off, w.selinfo_stride, (uint64_t)c->max_blocks * 8);
-    // wres: each window's merged, back-rotated result per column block
-    wregion(w.wres_off, w.wres_stride, (uint64_t)CMB_NCC * (c->nw + 1) * c->GP * CMB_RES * 4);
-    // pairs of more than 32 K blocks: the multi-workgroup top-k's histograms,
-    // radix states and per-chunk counts (chunks of 4096 blocks)
-    if (c->max_blocks > 32768) {
-        const uint64_t nch = ((uint64_t)c->max_blocks + 4095) / 4096;
-        wregion(w.tkx_off, w.tkx_stride, (3ull * 2048 + 16 + 2 * nch) * 4);
+    c->split_min = (int64_t)c->npairs * c->max_sel <= 1024ll * SPLIT_MIN ? SPLIT_FINE : SPLIT_MIN;
+    for (;; c->split_min = SPLIT_MIN) {
+        c->max_splits = (c->max_sel + c->split_min - 1) / c->split_min + c->nw + 1;
+        std::memset(&w, 0, sizeof(w));
+        off = 0;
+        auto wregion = [&](uint64_t &o, uint64_t &stride, uint64_t per_pair) {
+            stride = align256(per_pair);
+            o = off;
+            off = align256(off + stride * (uint64_t)c->npairs);
+        };
+        wregion(w.qrot_off, w.qrot_stride, (uint64_t)c->nw * D * c->GP * 4);
+        wregion(w.score_off, w.score_stride, (uint64_t)c->max_blocks * 4);
+        wregion(w.sel_off, w.sel_stride, (uint64_t)c->max_blocks * 4);
+        // wsel: window starts in the selected list, k, block count (pair 0: and
+        // the call's blocks per split)
+        wregion(w.wsel_off, w.wsel_stride, (uint64_t)(c->nw + 3) * 4);
+        // part: split partials (max, sum, unrotated accumulator per head)
+        wregion(w.part_off, w.part_stride, (uint64_t)c->max_splits * c->GP * (D + 2) * 4);
+        wregion(w.tag_off, w.tag_stride, (uint64_t)c->max_splits * 4);
+        wregion(w.binfo_off, w.binfo_stride, (uint64_t)c->max_blocks * 8);
+        wregion(w.bsize_off, w.bsize_stride, (uint64_t)c->max_blocks);
+        wregion(w.selinfo_off, w.selinfo_stride, (uint64_t)c->max_blocks * 8);
+        // wres: each window's merged, back-rotated result per column block
+        wregion(w.wres_off, w.wres_stride, (uint64_t)CMB_NCC * (c->nw + 1) * c->GP * CMB_RES * 4);
+        // pairs of more than 32 K blocks: the multi-workgroup top-k's histograms,
+        // radix states and per-chunk counts (chunks of 4096 blocks)
+        if (c->max_blocks > 32768) {
+            const uint64_t nch = ((uint64_t)c->max_blocks + 4095) / 4096;
+            wregion(w.tkx_off, w.tkx_stride, (3ull * 2048 + 16 + 2 * nch) * 4);
+        }
+        if (c->split_min == SPLIT_MIN || off <= MOSAIC_NOALLOC_SCRATCH_BYTES / 2) break;
     }
     w.total = off + 256;                     // whole 16-byte loads of the last pair's arrays stay inside
     w.max_blocks = c->max_blocks; w.max_splits = c->max_splits; w.gp = c->GP;
@@ -531,6 +540,11 @@ mosaic_status mosaic_decode_attention(mosaic_cache *c, const void *q, float *out
     }
     int nwu = std::max(1, std::min(c->nw, (maxL + c->P.rot_window - 1) / c->P.rot_window));
     Geom g = c->geom();
+    // tokens that the selections of all pairs take together
+    for (int q2 = 0; q2 < c->num_seqs; ++q2) {
+        const int64_t L = c->L[q2], n = L / SEG * SEG + ((L % SEG) >= UBUF ? UBUF : 0);
+        g.sel_tokens += c->P.num_kv_heads * std::min<int64_t>(n, (n * c->P.select_num + c->P.select_den - 1) / c->P.select_den);
+    }
     if (c->dyn) {
         // the windows in use as of the last poll: a window closed since then
         // is still empty (nothing is compressed before the poll), so it adds

@@ -156,9 +156,8 @@ constexpr int PLAN_W = 16;               // windows whose bounds a thread holds 
 // once (one round trip; the general functions above read them three times), every division is a multiplication, and the
 // thread that finds the workgroup's split publishes it.  Unlike the general
 // plan's splits of at least SPLIT_MIN blocks these go down to about 128
-// tokens, so short selections use the whole chip: one 4096-token sequence of 8
-// kv heads ran on 8 workgroups and now runs on 20; 4 x 32768 tokens with every
-// channel kept, 160 workgroups of 768 tokens, 81 us, now 410 of 128, 24 us
+// tokens, so short selections use the whole chip: 4 x 32768 tokens with every
+// channel kept, 160 workgroups of 768 tokens, 81 us, then 410 of 128, 24 us
 // (with the rows taken as the dense kernel takes them).  red: 16 words of LDS.
 __device__ __forceinline__ int plan_small(const Geom &g, const WsGeom &ws, int gidx, int *red, SplitJob *job) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = blockDim.x >> 6, lim = ws.max_blocks;
@@ -198,10 +197,10 @@ __device__ __forceinline__ int plan_small(const Geom &g, const WsGeom &ws, int g
     const int avail = max(ws.split_slots - et, max(ws.split_slots / 4, 1));
     // no split below about 128 tokens (a chunk for each of its waves) at the
     // blocks' mean size, nor so small that a pair's splits outgrow its array,
-    // which is sized for SPLIT_MIN blocks of the smallest size
+    // which is sized for split_min blocks of the smallest size
     const float tokens = (float)st * UBUF * g.sel_num / g.sel_den;
     const int b128 = (int)(128.0f * (float)kt / fmaxf(tokens, 1.0f) + 0.5f);
-    const int fit = (int)(((long long)nmax * SPLIT_MIN + ws.max_sel - 1) / ws.max_sel);
+    const int fit = (int)(((long long)nmax * ws.split_min + ws.max_sel - 1) / ws.max_sel);
     // more than SPLIT_MAX blocks for each resident workgroup: as many whole
     // rounds as that takes, of equal splits (a last round of a few splits
     // costs as much as a full one: a million tokens, 1037 splits of 128 blocks
@@ -395,7 +394,27 @@ k_attn(Geom g, WsGeom ws, float scale, const uint16_t *qraw) {
     // (pairs in order, each pair's splits in order); the grid covers every plan
     __shared__ SplitJob job;
     __shared__ int red[16];
-    if (g.npairs <= 64 * NWV && g.nw <= PLAN_W) {
+    if (ws.fix_splits) {
+        // one window: every pair has fix_splits places and one for its buffer,
+        // and a workgroup needs its own pair's counts only
+        SplitJob j;
+        j.p = blockIdx.x / (ws.fix_splits + 1);
+        const int i = blockIdx.x % (ws.fix_splits + 1);
+        const int32_t *wsel = wsel_of(ws, j.p);
+        j.L = g.meta_of(j.p)->L;
+        const int a = min(max(wsel[0], 0), ws.max_blocks), n = min(max(wsel[1], a), ws.max_blocks) - a;
+        const int sp = fixed_splits(g, ws, j.L, n);
+        const int rem = j.L % SEG;
+        j.buf = i == ws.fix_splits && rem - (rem >= UBUF ? UBUF : 0) > 0;
+        if (i == ws.fix_splits ? !j.buf : i >= sp) return;      // (the whole workgroup)
+        j.s = j.buf ? sp : i;
+        j.w = j.buf ? -2 : 0;
+        j.e0 = a + i;
+        j.stride = sp;
+        j.cnt = j.buf ? 0 : (n - i + sp - 1) / sp;
+        if (tid == 0) job = j;
+        lds_barrier();
+    } else if (g.npairs <= 64 * NWV && g.nw <= PLAN_W) {
         const int bps = plan_small(g, ws, blockIdx.x, red, &job);
         if (blockIdx.x == 0 && tid == 0) ws.wsel[g.nw + 2] = bps;    // for the combine (pair 0's list header)
     } else {
@@ -894,8 +913,9 @@ hipError_t attn_dt(const Geom &g, const WsGeom &w, float scale, const uint16_t *
     const long long whole = w.split_slots + (most > room ? most * w.split_slots / std::max<long long>(room, 1) : 0);
     const long long least = (long long)g.npairs * ceil_div(w.max_sel, SPLIT_LEAST);
     const long long nwg = std::min<long long>(std::min(whole, least) + extra, (long long)g.npairs * w.max_splits);
+    const unsigned grid = w.fix_splits ? (unsigned)(g.npairs * (w.fix_splits + 1)) : (unsigned)nwg;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(64 * ATTN_NWV), smem, s, g, w, scale, q);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * ATTN_NWV), smem, s, g, w, scale, q);
         return hipGetLastError();
     };
     // one strategy that keeps every channel: no record needs a walk

@@ -340,4 +340,13 @@ __device__ __forceinline__ int wave_max_i(int v) {
 
 template <int V> struct IntC { static constexpr int value = V; };
 
+// Splits of a pair's one window of k selected entries under the fixed plan:
+// its selected tokens in shares of split_tok, none empty, none above SPLIT_MAX
+// entries.  The attention and the combine derive the same number.
+__device__ __forceinline__ int fixed_splits(const Geom &g, const WsGeom &ws, int L, int k) {
+    const float tok = (float)(L / UBUF * UBUF) * (float)g.sel_num / (float)g.sel_den;
+    const int s = max((int)(tok / ws.split_tok) + 1, (k + SPLIT_MAX - 1) / SPLIT_MAX);
+    return min(min(s, ws.fix_splits), k);
+}
+
 }  // namespace mosaic

@@ -15,6 +15,7 @@ constexpr int WAVE = 64;
 // block table)
 constexpr int SPLIT_MIN = 48;
 constexpr int SPLIT_MAX = 128;
+constexpr int SPLIT_FINE = 16;    // the same where the selections are short (smaller workspaces have room for it)
 constexpr int SPLIT_LEAST = 8;    // blocks of the smallest split (short selections; see the attention's plan)
 constexpr int ATTN_NWV = 2;       // waves per attention workgroup
 constexpr int ATTN_WPE = 2;       // waves per SIMD the attention's registers allow
@@ -63,6 +64,7 @@ struct Geom {
     int dyn;                          // windows of decode tokens closed by their loss
     int min_win;                      // tokens a window holds before a loss close
     float tau_win;                    // accumulated loss that closes a window
+    long long sel_tokens;             // decode: tokens that the call's selections take together
 
     __host__ __device__ PairMeta *meta_of(int p) const { return (PairMeta *)(meta + (uint64_t)p * meta_stride); }
     // a pair's descriptor, score and token regions, from the pair table (one
@@ -102,6 +104,9 @@ struct WsGeom {               // decode workspace
     uint32_t *tkx; uint64_t tkx_stride;     // multi-workgroup top-k state, or null (pairs of <= 16 K blocks)
     int max_blocks, max_splits, max_sel;
     int split_slots;                        // attention workgroups resident at once on the device
+    int split_min;                          // blocks of the smallest split that max_splits has room for
+    int fix_splits;                         // splits of a pair at most under the fixed plan, 0 without it
+    float split_tok;                        // tokens of a split under the fixed plan
 };
 
 // First segment of window w of pair p: every W tokens, or from the window
