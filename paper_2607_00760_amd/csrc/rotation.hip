@@ -126,6 +126,9 @@ __global__ void __launch_bounds__(256) k_cov(const uint16_t *k, const uint16_t *
 // position i of step s of the round-robin tournament over 128 indices
 __device__ __forceinline__ int rr_index(int i, int s) { return i == 0 ? 0 : 1 + (i - 1 + s) % (D - 1); }
 
+// the index at a position one step later
+__device__ __forceinline__ int rr_next(int i) { return i == 0 ? 0 : (i == D - 1 ? 1 : i + 1); }
+
 constexpr int JT = 1024;          // threads of a solver workgroup
 
 // sum over the JT threads of the block (fixed order); red: JT / 64 floats of LDS
@@ -161,9 +164,11 @@ __device__ __forceinline__ void jacobi_params(const float *A, int p, int q, floa
 // row pairs' in scalar ones; V stays in registers, its columns moving between
 // lanes as the tournament moves them, so only A goes through LDS; and the next
 // step's rotations (a chain of divisions and square roots) are computed while
-// V takes this step's.  64 matrices: 2.98 ms with everything in LDS, 2.69 with
-// the indices and rotations in registers, 2.35 now, bit for bit the same.  (All of a thread's loads of
-// A before its first store measured no faster.)
+// V takes this step's; indices move on by one each step instead of being taken
+// modulo 127 again (four divisions by a constant a thread and step).  64
+// matrices: 2.98 ms with everything in LDS, 2.69 with the indices and rotations
+// in registers, 2.35 with V in them, 2.15 now, bit for bit the same.  (All of a
+// thread's loads of A before its first store measured no faster.)
 __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int W, int nw, int nslices,
                                                 const float *part, float *rot_k, float *rot_v, float *ev_k,
                                                 float *ev_v) {
@@ -221,6 +226,13 @@ __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int 
         __syncthreads();
         if (s_done) break;
         if (wave == 0) jacobi_params(A, min(f, g2), max(f, g2), rcs[0][lane]);
+        constexpr int NB = 64 * 64 / JT;                       // row pairs of a wave: wave, wave + 16, ...
+        int fk[NB], gk[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            fk[j] = rr_index(wave + j * (JT / 64), 0);
+            gk[j] = rr_index(D - 1 - wave - j * (JT / 64), 0);
+        }
         __syncthreads();
         for (int st = 0; st < D - 1; ++st) {
             const int pm = min(f, g2), qm = max(f, g2);
@@ -246,8 +258,7 @@ __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int 
 #pragma unroll
             for (int j = 0; j < 64 * 64 / JT; ++j) {
                 const int kk = wave + j * (JT / 64);           // wave-uniform: the row pair sits in scalar registers
-                const int fk = rr_index(kk, st), gk = rr_index(D - 1 - kk, st);
-                float *rp = A + min(fk, gk) * JP, *rq = A + max(fk, gk) * JP;
+                float *rp = A + min(fk[j], gk[j]) * JP, *rq = A + max(fk[j], gk[j]) * JP;
                 const float ck = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cs[kk].x)));
                 const float sk = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cs[kk].y)));
                 const float bpp = rp[pm], bpq = rp[qm], bqp = rq[pm], bqq = rq[qm];
@@ -262,8 +273,10 @@ __global__ void __launch_bounds__(JT) k_jacobi(const int32_t *ctx, int hkv, int 
             __syncthreads();
             // the next step's rotations from wave 0 while the others apply this step's to V
             if (wave != 0) turn_v();
-            f = lane == 0 ? 0 : (f == D - 1 ? 1 : f + 1);
-            g2 = g2 == D - 1 ? 1 : g2 + 1;
+            f = rr_next(f);
+            g2 = rr_next(g2);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) { fk[j] = rr_next(fk[j]); gk[j] = rr_next(gk[j]); }
             if (wave == 0 && st + 1 < D - 1) jacobi_params(A, min(f, g2), max(f, g2), rcs[(st + 1) & 1][lane]);
             __syncthreads();
         }
