@@ -196,7 +196,9 @@ mosaic_status mosaic_workspace_bytes(const mosaic_cache *cache, int32_t op, size
  *   wsel  + p * wsel_stride  : int32 [windows + 3]: first selected entry of
  *                              each window, then k, then the block count;
  *                              for pair 0 then the call's selected blocks
- *                              per split-K partition
+ *                              per split-K partition (calls of one-window
+ *                              caches may plan the splits on the host and
+ *                              leave it as it is)
  *   part  + p * part_stride  : fp32 [max_splits][GP * (D + 2)]: split-K
  *                              partials (max, sum, accumulator per head; a
  *                              window's splits hold it in the window's
@@ -213,7 +215,9 @@ mosaic_status mosaic_workspace_bytes(const mosaic_cache *cache, int32_t op, size
  *                              block of 16 output columns and each window
  *                              (the last slot: the update buffer), the
  *                              window's merged max and sum per head and its
- *                              back-rotated output columns
+ *                              back-rotated output columns (not written for
+ *                              caches of one or two windows, whose combine
+ *                              merges them itself)
  * Calls that overlap on one workspace race; separate streams need separate
  * workspaces. */
 typedef struct {

@@ -10,7 +10,7 @@
 //            the bins follow the keys that are present (at most three passes
 //            reach a single key), then an ordered compaction that breaks ties
 //            by the lowest block index.  Up to 32768 blocks per pair the keys
-//            stay in registers (16 or 32 per thread, one workgroup per pair);
+//            stay in registers (4 to 32 per thread, one workgroup per pair);
 //            scans and reductions use lane shifts inside the wave.  Longer
 //            pairs are spread over workgroups of 4096 blocks, one kernel per
 //            phase.

@@ -8,15 +8,15 @@
 //              16-bit operands: every product is exact, fp32 accumulation)
 //              over 4096-token slices; the solver sums the slices in slice
 //              order, so the result does not depend on scheduling.
-//   k_jacobi : one 1024-thread workgroup per matrix: A and the accumulated rotations V in
-//              LDS (rows padded to 129 floats), cyclic Jacobi with the
+//   k_jacobi : one 1024-thread workgroup per matrix: A in LDS (rows padded to
+//              129 floats), the accumulated rotations V in registers (in LDS
+//              only to be ranked and written), cyclic Jacobi with the
 //              round-robin ordering that pairs all 128 indices into 64
 //              disjoint rotations per step (127 steps per sweep), A updated
 //              one 2 x 2 block (rows of one pair, columns of another) per
 //              thread and V by columns in the same pass, sweeps until the
 //              off-diagonal energy is below 1e-12 of the diagonal's (at most
-//              30).  Then the
-//              eigenvalues are ranked (descending, index ascending on ties)
+//              30).  Then the eigenvalues are ranked (descending, index ascending on ties)
 //              and each eigenvector is written as row rank of R, normalized
 //              and signed so that its largest-magnitude component is
 //              positive.

@@ -323,7 +323,9 @@ __global__ void __launch_bounds__(1024) k_front(Geom g, WsGeom ws, const uint16_
     const PairMeta meta = *g.meta_of(p);
     if (tid < 8 * D) qraw[tid / D][tid % D] = tid < G * D ? h2f(q[(uint64_t)p * G * D + tid], g.dtype) : 0.0f;
     int nf, prov, nbuf;
-    const int ndesc = pair_ndesc(meta, nf, prov, nbuf);
+    // (the host admits no more: a captured call replayed on a cache that grew
+    // since stays inside the arrays)
+    const int ndesc = min(pair_ndesc(meta, nf, prov, nbuf), FRONT_SEGS);
     if (tid < ndesc) {
         const Desc d = g.desc_of(p)[tid];
         ds[tid] = d;
