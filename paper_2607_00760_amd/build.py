@@ -2,7 +2,7 @@
 
 All HIP sources are compiled with fp contraction off (every fused multiply-add
 in the kernels is an explicit fmaf) and with the packed-fp32 instructions
-disabled.
+disabled.  A HIP error that is dropped without saying so does not compile.
 """
 from __future__ import annotations
 
@@ -20,7 +20,7 @@ SOURCES = ["api.hip", "attn_bf16_g4.hip", "attn_bf16_g8.hip", "attn_fp16_g4.hip"
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
+    "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Werror=unused-value",
 ]
 
 

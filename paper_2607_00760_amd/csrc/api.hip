@@ -413,7 +413,7 @@ mosaic_status mosaic_cache_bind(mosaic_cache *c, void *arena, size_t bytes) {
 
 mosaic_status mosaic_cache_destroy(mosaic_cache *c) {
     if (c && c->ev[0])
-        for (auto &e : c->ev) hipEventDestroy(e);
+        for (auto &e : c->ev) (void)hipEventDestroy(e);
     delete c;
     return ok();
 }

@@ -1064,9 +1064,13 @@ hipError_t launch_compress(const Geom &g, const uint16_t *k, const uint16_t *v, 
     hipLaunchKernelGGL(k_scan, dim3(g.npairs), dim3(256), 0, s, g, 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (max_full_segs > 0) {
-        if (ws) hipLaunchKernelGGL(k_compact, grid, dim3(256), 0, s, g, (const uint8_t *)ws, slot_tok, slot_sc);
-        else launch_prefill(g, 1, k, v, seq_stride, ws, slot_tok, slot_sc, max_full_segs, 0, s);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (ws) {
+            hipLaunchKernelGGL(k_compact, grid, dim3(256), 0, s, g, (const uint8_t *)ws, slot_tok, slot_sc);
+            e = hipGetLastError();
+        } else {                                // (hands its launch's error over: a later hipGetLastError sees none)
+            e = launch_prefill(g, 1, k, v, seq_stride, ws, slot_tok, slot_sc, max_full_segs, 0, s);
+        }
+        if (e != hipSuccess) return e;
     }
     if (any_tail) {
         hipLaunchKernelGGL(k_stage_tail, dim3(g.npairs), dim3(256), 0, s, g, k, v, seq_stride);

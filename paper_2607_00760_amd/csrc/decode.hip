@@ -650,7 +650,7 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
         const int r = i < 3 ? g.keep_cand[i] : g.def_keep;
         fixed = fixed && (r == 16 || r == 32 || r == 48);
     }
-    if (ev) hipEventRecord(ev[0], s);
+    if (ev) (void)hipEventRecord(ev[0], s);
     // blocks of a pair at most in this call: its segments times the most
     // blocks a segment can have
     int minb = g.def_block;
@@ -677,15 +677,15 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
     if (fixed && g.nw == 1 && maxb <= FRONT_BLOCKS) {
         // a short context: rotation, scores and selection of a pair by one
         // workgroup (timed as the scoring)
-        if (ev) hipEventRecord(ev[1], s);
+        if (ev) (void)hipEventRecord(ev[1], s);
         if ((e = launch_front(g, w, q, s)) != hipSuccess) return e;
-        if (ev) hipEventRecord(ev[2], s);
+        if (ev) (void)hipEventRecord(ev[2], s);
     } else {
         hipLaunchKernelGGL(k_qrot, dim3(nwq * (D / QROT_COLS), g.npairs), dim3(256), 0, s, g, w, q);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (ev) hipEventRecord(ev[1], s);
+        if (ev) (void)hipEventRecord(ev[1], s);
         if (max_desc_used > 0 && (e = launch_score(g, w, max_desc_used, fixed, small, s)) != hipSuccess) return e;
-        if (ev) hipEventRecord(ev[2], s);
+        if (ev) (void)hipEventRecord(ev[2], s);
         if (maxb > 1024 * TOPK_KPT_MAX) {
             if (!w.tkx) return hipErrorInvalidValue;               // the workspace has no multi-workgroup state
             const int nch = ceil_div(w.max_blocks, TKM_CHUNK);
@@ -705,11 +705,11 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     }
-    if (ev) hipEventRecord(ev[3], s);
+    if (ev) (void)hipEventRecord(ev[3], s);
     if (g.dtype) e = GP == 4 ? launch_attn_bf16_g4(g, w, scale, q, fixed, small, s) : launch_attn_bf16_g8(g, w, scale, q, fixed, small, s);
     else e = GP == 4 ? launch_attn_fp16_g4(g, w, scale, q, fixed, small, s) : launch_attn_fp16_g8(g, w, scale, q, fixed, small, s);
     if (e != hipSuccess) return e;
-    if (ev) hipEventRecord(ev[4], s);
+    if (ev) (void)hipEventRecord(ev[4], s);
     const int wgs = (g.npairs + 7) / 8 * 8 * CMB_NCC;
     if (g.nw <= 2) {                           // few slots per output: one kernel
         if (g.nw == 1) hipLaunchKernelGGL((k_combine<GP, 2>), dim3(wgs), dim3(2 * CMB_THREADS), 0, s, g, w, out);
@@ -721,7 +721,7 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
         hipLaunchKernelGGL(k_merge<GP>, dim3(ceil_div(g.npairs * GP * D, 256)), dim3(256), 0, s, g, w, out);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (ev) hipEventRecord(ev[5], s);
+    if (ev) (void)hipEventRecord(ev[5], s);
     return hipSuccess;
 }
 
