@@ -150,6 +150,7 @@ struct SplitJob {
     int p, s, w, e0, stride, cnt, L, buf;
 };
 constexpr int PLAN_W = 16;               // windows whose bounds a thread holds in registers
+__host__ __device__ __forceinline__ bool register_plan(const Geom &g) { return g.npairs <= 64 * ATTN_NWV && g.nw <= PLAN_W; }
 
 // The plan and this workgroup's place in it, for at most blockDim.x pairs of
 // at most PLAN_W windows: thread p loads pair p's length and window bounds
@@ -414,7 +415,7 @@ k_attn(Geom g, WsGeom ws, float scale, const uint16_t *qraw) {
         j.cnt = j.buf ? 0 : (n - i + sp - 1) / sp;
         if (tid == 0) job = j;
         lds_barrier();
-    } else if (g.npairs <= 64 * NWV && g.nw <= PLAN_W) {
+    } else if (register_plan(g)) {
         const int bps = plan_small(g, ws, blockIdx.x, red, &job);
         if (blockIdx.x == 0 && tid == 0) ws.wsel[g.nw + 2] = bps;    // for the combine (pair 0's list header)
     } else {
@@ -902,15 +903,20 @@ k_attn(Geom g, WsGeom ws, float scale, const uint16_t *qraw) {
 
 template <int DT, int GP>
 hipError_t attn_dt(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s) {
-    // the plan has at most as many splits of whole blocks as fill its rounds
-    // (rounds - 1 of them hold SPLIT_MAX blocks for each workgroup) plus one rounding split per window and per buffer,
-    // and never more than every pair's whole partial array or the most blocks
-    // that can be selected in splits of SPLIT_LEAST
+    // Workgroups past the last split derive the plan and end, so the grid is no
+    // larger than the plan that the kernel takes can need.  The register plan
+    // has as many splits as whole rounds of the resident workgroups, the general
+    // one as fill a single round or as splits of SPLIT_MAX blocks, both with one
+    // rounding split more per window and buffer; and never more than every pair's
+    // whole partial array or the most blocks that can be selected in splits of
+    // SPLIT_LEAST.  (Sized by rounds for both, and by a round more than needed,
+    // one sequence of 60000 tokens beside 31 of 500 launched 7680 workgroups of
+    // the general plan, 82 us in this kernel; 3584 take 46.)
     const size_t smem = ATTN_HDR_BYTES + (size_t)ATTN_NWV * TILE_BYTES;
     const long long extra = (long long)g.npairs * (g.nw + 1);
-    const long long room = std::max<long long>(w.split_slots - extra, w.split_slots / 4);    // (the plan's, at least)
     const long long most = (long long)g.npairs * ceil_div(w.max_sel, SPLIT_MAX);
-    const long long whole = w.split_slots + (most > room ? most * w.split_slots / std::max<long long>(room, 1) : 0);
+    const long long room = std::max<long long>(std::max<long long>(w.split_slots - extra, w.split_slots / 4), 1);    // (the plan's, at least)
+    const long long whole = register_plan(g) ? (most + room - 1) / room * w.split_slots : std::max<long long>(w.split_slots, most);
     const long long least = (long long)g.npairs * ceil_div(w.max_sel, SPLIT_LEAST);
     const long long nwg = std::min<long long>(std::min(whole, least) + extra, (long long)g.npairs * w.max_splits);
     const unsigned grid = w.fix_splits ? (unsigned)(g.npairs * (w.fix_splits + 1)) : (unsigned)nwg;

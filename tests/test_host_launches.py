@@ -1,11 +1,14 @@
 """The library's real launch code on the CPU, over a recording HIP runtime
 (tests/hostsim/fake_runtime.cpp): every entry point runs once with all its
 launches and copies succeeding, then once for each of them failing, and must
-report the failure each time."""
+report the failure each time; and the attention's grid covers every split plan
+that the kernel can derive, with little to spare."""
 from __future__ import annotations
 
 import ctypes as C
+import mmap
 import os
+import random
 import struct
 import sys
 
@@ -55,8 +58,8 @@ class Sim:
         else:
             assert self.L.mosaic_cache_create_ragged(C.byref(p), len(lens), (C.c_int32 * len(caps))(*caps), rotated, C.byref(h)) == OK
         assert self.L.mosaic_cache_arena_bytes(h, C.byref(n)) == OK
-        raw = C.create_string_buffer(n.value + 256)
-        arena = (C.addressof(raw) + 255) // 256 * 256
+        raw = mmap.mmap(-1, n.value + 4096)                 # (page-aligned, and only touched pages take memory)
+        arena = C.addressof(C.c_char.from_buffer(raw))
         assert self.L.mosaic_cache_bind(h, C.c_void_p(arena), n.value) == OK
         self.keep = self.keep[:1] + [raw]
         return dict(h=h, p=p, lens=lens, rotated=rotated, arena=arena)
@@ -191,3 +194,73 @@ def test_every_failed_launch_is_reported(sim, name):
     for i, (what, _) in enumerate(calls):
         st, _, message = once(i)
         assert st == HIP and message, f"{name}: call {i} ({what}) failed, status {st}"
+
+
+# ---------------------------------------------------------------- the attention's grid
+SLOTS, SPLIT_MIN, SPLIT_MAX, SPLIT_FINE, SPLIT_LEAST = 1024, 48, 128, 16, 8     # 256 CUs, 4 workgroups each
+
+
+def _splits_of_plan(small, lens, windows, max_sel, max_splits, split_min):
+    """The number of splits that the attention's plan makes of these selected
+    entries per window of each pair (windows[p]), update buffers included."""
+    kt = sum(sum(n) for n in windows)
+    buffers = sum(1 for L in lens if L % 64 - (32 if L % 64 >= 32 else 0) > 0)
+    et = buffers + sum(1 for n in windows for x in n if x)
+    avail = max(SLOTS - et, SLOTS // 4)
+    if small:
+        tokens = sum(L // 32 for L in lens) * 32 / 10
+        b128 = int(128 * kt / max(tokens, 1) + 0.5)
+        fit = -(-max(sum(n) for n in windows) * split_min // max_sel)
+        rounds = -(-kt // (avail * SPLIT_MAX))
+        room = rounds * SLOTS - min(et, SLOTS) if rounds > 1 else avail
+        bps = min(max(-(-kt // room), fit, min(max(b128, SPLIT_LEAST), SPLIT_MIN)), SPLIT_MAX)
+    else:
+        bps = min(max(-(-kt // avail), SPLIT_MIN), SPLIT_MAX)
+    return buffers + sum(-(-x // bps) for n in windows for x in n)
+
+
+# lengths, kv heads, rotation window: both plans, one or more rounds, even and uneven lengths
+GRIDS = {
+    "batch_two_windows": ([32768] * 4, 8, 16384), "long_batch": ([131072] * 8, 8, 65536), "long_one": ([1 << 20], 8, 65536),
+    "long_one_room": ([(1 << 20) + 64], 8, 65536), "uneven_many": ([60000] + [500] * 31, 8, 65536),
+    "uneven_many_two_windows": ([100000] + [100] * 31, 8, 65536), "at_128_pairs": ([9000 + 70 * i for i in range(32)], 4, 4096),
+    "past_128_pairs": ([9000 + 70 * i for i in range(33)], 4, 4096), "windows_16": ([16000], 8, 1024), "windows_17": ([17000], 8, 1024),
+    "short_many": ([40 + i for i in range(64)], 8, 64), "short_few": ([1000, 333], 2, 512),
+}
+
+
+@pytest.mark.parametrize("name", list(GRIDS))
+def test_attention_grid_covers_the_plan_and_little_more(sim, name):
+    lens, hkv, W = GRIDS[name]
+    sim.L.fake_reset(-1)
+    c = sim.cache(lens, rot_window=W, num_kv_heads=hkv)
+    lay = _lib.MosaicWsLayout()
+    assert sim.L.mosaic_decode_ws_layout(c["h"], C.byref(lay)) == OK
+    assert sim.compress(c) == OK
+    sim.L.fake_reset(-1)
+    assert sim.decode(c) == OK
+    grid = next(g[0] for what, g in sim.calls() if "k_attn" in what)
+    assert sim.L.mosaic_cache_destroy(c["h"]) == OK
+    nw, npairs = -(-max(lens) // W), len(lens) * hkv
+    small = npairs <= 128 and nw <= 16
+    desc = max(lens) // 64 + 2
+    max_sel = min(16 * desc, -(-(-(-desc * 64 // 10)) // 4) + 1)
+    split_min = next(m for m in (SPLIT_MIN, SPLIT_FINE) if lay.max_splits == -(-max_sel // m) + nw + 1)
+    pair_lens = [L for L in lens for _ in range(hkv)]
+    rng = random.Random(name)
+    for blocks in (4, 8, 16, 0):                             # tokens of a block; 0: any number of entries
+        for _ in range(20):
+            windows = []
+            for L in pair_lens:
+                k = rng.randint(0, max_sel) if blocks == 0 else min(max_sel, -(-L // 10 // blocks))
+                cut = sorted(rng.randint(0, k) for _ in range(nw - 1))
+                windows.append([b - a for a, b in zip([0] + cut, cut + [k])])
+            need = _splits_of_plan(small, pair_lens, windows, max_sel, lay.max_splits, split_min)
+            assert need <= grid, f"{name}: {need} splits for {grid} workgroups"
+    # what a plan of this call can need: its rounds of resident workgroups (the
+    # general plan: one, or splits of the largest size), a rounding split for
+    # every window and buffer
+    extra = npairs * (nw + 1)
+    full = npairs * -(-max_sel // SPLIT_MAX)
+    rounds = -(-full // max(SLOTS - extra, SLOTS // 4)) if small else 1
+    assert grid <= max(rounds * SLOTS, 0 if small else full) + extra, f"{name}: {grid} workgroups"
