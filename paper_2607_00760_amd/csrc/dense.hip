@@ -7,8 +7,9 @@
 // straight into matrix-core operands (a lane's 16 bytes of a row are 8
 // channels of the product's inner dimension), V rows go by direct loads into
 // LDS, from where the transposing reads hand them to the second product, and
-// both are loaded one step ahead.  The weights take part as two fp16 or three
-// bf16 parts (22 and 24 bits), so the sums stay at fp32 accuracy.
+// both are loaded one step ahead.  The weights take part as three 16-bit parts,
+// which hold all 24 bits of the fp32 weight in either type; with up to four
+// heads the parts share one product, so the third costs nothing.
 // 4 x 32768 tokens, 8 kv heads, bf16 (537 MB): lane-per-token dot products on
 // the vector ALU took 200 us (2.7 TB/s); this takes 101 us (5.3 TB/s).
 #include "dense_step.h"
@@ -99,7 +100,7 @@ k_dense_split(const uint16_t *q, const uint16_t *k, const uint16_t *v, int hkv, 
                 for (int r = 0; r < 4; ++r)
                     if (t + 16 * n + 4 * q4 + r >= t1) z[n][r] = -INFINITY;
         }
-        dense_accumulate<DT, GP, DT ? 3 : 2>(z, m_run, l_run, acc, PS, [&] {
+        dense_accumulate<DT, GP, 3>(z, m_run, l_run, acc, PS, [&] {
             // this step's V rows have landed once only the next step's 8 + 8 loads are out
             asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         }, va, buf * VBUF);
@@ -122,7 +123,7 @@ k_dense_split(const uint16_t *q, const uint16_t *k, const uint16_t *v, int hkv, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) mrg[(4 * q4 + r) * (D + 2) + 2 + 16 * ct + l16] = acc[ct][r];
     __syncthreads();
-    constexpr int NROW = (DT && GP == 4) ? 3 : 2;              // rows of a head in the accumulator
+    constexpr int NROW = GP == 4 ? 3 : 2;              // rows of a head in the accumulator
     float *out = part + ((uint64_t)p * max_splits + sp) * GP * (D + 2);
     for (int i = tid; i < GP * D; i += 64 * DNWV) {
         const int h = i / D, c = i % D;

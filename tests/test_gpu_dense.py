@@ -1,7 +1,7 @@
 """Dense decode attention at the edges of its 32-token steps, its 128-token
 rounds and its 1024-token runs, for every width of the group's padding,
 against the fp64 oracle.  Logits and sums are fp32 over exact 16-bit products
-and the weights carry 22 or 24 bits, so 2e-6 relative covers them with the
+and the weights carry 24 bits, so 2e-6 relative covers them with the
 exponential's error (a few ulp of logits below 2^4)."""
 import numpy as np
 import pytest
@@ -32,3 +32,37 @@ def test_dense_edges(dtype, G):
         want = O.dense_attention(bits(q)[b], bits(lay["k"])[b, 0, :L], bits(lay["v"])[b, 0, :L], np.float32(scale_of()), dtype)
         rel = np.linalg.norm(got - want) / np.linalg.norm(want)
         assert rel < 2e-6, f"L={L} G={G} {dtype}: rel {rel:.2e}"
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("G", [4, 8])
+def test_dense_weights_keep_24_bits(dtype, G):
+    """Sequences of two tokens: weights 1 and w = exp(-x), w in (1/2, 1).  With
+    V = a in the first token and -1 in the second, a the 16-bit value nearest to
+    w, the output (a - w') / (1 + w) gives the weight w' that took part to
+    2^-33, as a - w' is below 2^-8 and the output has 24 bits.  An fp32 weight
+    in (1/2, 1) is a multiple of 2^-24, an odd one half of the time; two fp16
+    parts leave an even one wherever the second part is 2^-13 or more (its last
+    place is then 2^-23 or more), and two bf16 parts lose more still."""
+    S, dt = 64, torch.float16 if dtype == "fp16" else torch.bfloat16
+    rng = np.random.RandomState(3)
+    q = torch.zeros(S, G, 128)
+    q[:, :, 0] = torch.from_numpy(rng.randint(64, 128, (S, G)) / 128.0)      # exact in both types
+    k, v = torch.zeros(S, 1, 2, 128), torch.zeros(S, 1, 2, 128)
+    k[:, 0, 1, 0] = -torch.from_numpy(rng.randint(16, 88, S) / 128.0)
+    z = (q[:, :, 0] * k[:, 0, 1, :1]).double().numpy()                       # [S][G]
+    a = torch.from_numpy(np.exp(z)).to(dt)
+    v[:, 0, 0, :G], v[:, 0, 1] = a.float(), -1.0
+    out = M.dense_decode(q.to(dt).cuda(), k.to(dt).cuda(), v.to(dt).cuda(), torch.full((S,), 2, dtype=torch.int32, device="cuda"),
+                         1.0, 2, G).cpu().double()
+    got = torch.diagonal(out[:, :, :G], dim1=1, dim2=2).numpy()              # head h's channel h
+    a = a.double().numpy()
+    w = np.exp(z)
+    for _ in range(3):
+        w = a - got * (1.0 + w)
+    assert np.abs(w / np.exp(z) - 1.0).max() < 4 * 2.0 ** -23                # the exponential's own error
+    n = w * 2.0 ** 24
+    assert np.abs(n - np.round(n)).max() < 0.05
+    wide = np.abs(w - a) >= 2.0 ** -13
+    odd = np.round(n).astype(np.int64)[wide] % 2
+    assert wide.sum() > 64 and odd.mean() > 0.25, f"{odd.sum()} odd of {wide.sum()}"
