@@ -86,14 +86,15 @@ __device__ __forceinline__ void dense_accumulate(float (&z)[2][4], float &m_run,
 #pragma unroll
         for (int r = 0; r < 4; ++r) cm = fmaxf(cm, z[n][r]);
     cm = rows_all(cm, [](float a, float b) { return fmaxf(a, b); });
-    const float mn = fmaxf(m_run, cm);                     // finite: every step holds a token
-    const float alpha = __expf(m_run - mn);
+    const float mn = fmaxf(m_run, cm);
+    const float mb = mn == -INFINITY ? 0.0f : mn;          // no token but masked ones (logit -inf) yet: weights 0
+    const float alpha = __expf(m_run - mb);
     float ls = 0.0f;
 #pragma unroll
     for (int n = 0; n < 2; ++n)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            z[n][r] = __expf(z[n][r] - mn);
+            z[n][r] = __expf(z[n][r] - mb);
             ls += z[n][r];
         }
     ls = rows_all(ls, [](float a, float b) { return a + b; });

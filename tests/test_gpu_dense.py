@@ -66,3 +66,35 @@ def test_dense_weights_keep_24_bits(dtype, G):
     wide = np.abs(w - a) >= 2.0 ** -13
     odd = np.round(n).astype(np.int64)[wide] % 2
     assert wide.sum() > 64 and odd.mean() > 0.25, f"{odd.sum()} odd of {wide.sum()}"
+
+
+def _softmax64(q, k, v):
+    """[G][128], fp64: attention of q [G][128] over k, v [n][128], scale 1 / sqrt(128)."""
+    z = q.double() @ k.double().T * float(scale_of())
+    return (torch.softmax(z, 1) @ v.double()).numpy()
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("G", [4, 7])
+def test_dense_masked_tokens(dtype, G):
+    """Tokens masked through their keys, to a logit of -inf or to the type's
+    lowest value: whole 32-token steps, a wave's first steps, whole 1024-token
+    runs, all but the last token.  They take no part, so the result is the
+    attention over the others (bound as above)."""
+    dt = torch.float16 if dtype == "fp16" else torch.bfloat16
+    masks = [(0, 32), (0, 64), (0, 300), (32, 160), (0, 1024), (0, 1100), (1024, 2048), (0, 2499), (1, 2500)]
+    S, n = len(masks), 2500
+    g = torch.Generator().manual_seed(7)
+    q, k, v = (torch.randn(*sh, 128, generator=g).to(dt) for sh in ((S, G), (S, 1, n), (S, 1, n)))
+    q[:, :, 0] = 1.0
+    lens = torch.full((S,), n, dtype=torch.int32, device="cuda")
+    for mask in (-float("inf"), torch.finfo(dt).min):
+        kk = k.clone()
+        for s, (a, b) in enumerate(masks):
+            kk[s, 0, a:b, 0] = mask
+        out = M.dense_decode(q.cuda(), kk.cuda(), v.cuda(), lens, scale_of(), n, G).cpu().double().numpy()
+        for s, (a, b) in enumerate(masks):
+            keep = [t for t in range(n) if not a <= t < b]
+            want = _softmax64(q[s], k[s, 0, keep], v[s, 0, keep])
+            rel = np.linalg.norm(out[s] - want) / np.linalg.norm(want)
+            assert rel < 2e-6, f"{dtype} G={G} mask {mask} of {a}..{b}: rel {rel:.2e}"
