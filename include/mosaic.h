@@ -23,6 +23,10 @@
  *    cause.
  *  - head_dim is 128.  K, V and q share one element type: fp16 or bf16,
  *    little-endian 16-bit.  Outputs are fp32.
+ *  - The compressed path (compress, append, decode, rotations, reorder) takes
+ *    finite K, V, q and rotations.  The dense baseline takes any: tokens of
+ *    logit -inf weigh nothing, an infinite V element of positive weight gives
+ *    its infinity.
  *  - A cache holds num_seqs sequences x num_kv_heads kv heads.  Query head h
  *    of a sequence reads kv head h / group_size (GQA).
  */

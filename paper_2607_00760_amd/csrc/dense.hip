@@ -123,10 +123,14 @@ k_dense_split(const uint16_t *q, const uint16_t *k, const uint16_t *v, int hkv, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) mrg[(4 * q4 + r) * (D + 2) + 2 + 16 * ct + l16] = acc[ct][r];
     __syncthreads();
-    constexpr int NROW = GP == 4 ? 3 : 2;              // rows of a head in the accumulator
+    constexpr int NROW = GP == 4 ? 3 : 2;                      // rows of a head in the accumulator
+    constexpr int NT = 64 * DNWV, NE = GP * D / NT;            // outputs of a thread
+    __shared__ float mx[GP];                                   // each head's maximum
     float *out = part + ((uint64_t)p * max_splits + sp) * GP * (D + 2);
-    for (int i = tid; i < GP * D; i += 64 * DNWV) {
-        const int h = i / D, c = i % D;
+    bool odd = false;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const int i = tid + e * NT, h = i / D, c = i % D;
         float M = -INFINITY;
         for (int x = 0; x < DNWV; ++x) M = fmaxf(M, ((const float *)vt[x][0])[h * (D + 2)]);
         float A = 0.0f, Ls = 0.0f;
@@ -140,9 +144,55 @@ k_dense_split(const uint16_t *q, const uint16_t *k, const uint16_t *v, int hkv, 
             Ls += mw[h * (D + 2) + 1] * f;
         }
         out[2 * GP + h * D + c] = A;
-        if (c == 0) { out[h] = M; out[GP + h] = Ls; }
+        if (c == 0) { out[h] = M; out[GP + h] = Ls; mx[h] = M; }
+        odd |= h < G && !(fabsf(A) < INFINITY);
     }
+    // A weight in parts times an infinite element is an infinity of either sign
+    // or NaN, where the weight itself gives the element's infinity: the run's
+    // sums again, with whole weights on the vector ALU (rare; about the 200 us
+    // that 4 x 32768 tokens took in this form).
+    if (!__syncthreads_or(odd)) return;
+    float *wt = (float *)&vt[0][0][0];                         // [NT][GP]: a token's weights
+    float a[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) a[e] = 0.0f;
+#pragma unroll 1
+    for (int b = t0; b < t1; b += NT) {
+        if (b + tid < t1) {
+            const uint4 *row = (const uint4 *)(kp + (uint64_t)(b + tid) * D);
+            float z[GP];
+#pragma unroll
+            for (int h = 0; h < GP; ++h) z[h] = 0.0f;
+#pragma unroll 1
+            for (int x = 0; x < D / 8; ++x) {
+                const uint4 u = row[x];
+                const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float kv = h2f((uint16_t)((i & 1) ? (w4[i >> 1] >> 16) : w4[i >> 1]), DT);
+#pragma unroll
+                    for (int h = 0; h < GP; ++h)
+                        if (h < G) z[h] = fmaf(h2f(q[((uint64_t)p * G + h) * D + 8 * x + i], DT), kv, z[h]);
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < GP; ++h) wt[tid * GP + h] = mx[h] == -INFINITY ? 0.0f : __expf(z[h] * scale - mx[h]);
+        }
+        __syncthreads();
+        const int n = min(NT, t1 - b);
+#pragma unroll 1
+        for (int t2 = 0; t2 < n; ++t2)
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const int i = tid + e * NT;
+                a[e] = fmaf(wt[t2 * GP + i / D], h2f(vp[(uint64_t)(b + t2) * D + i % D], DT), a[e]);
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e) out[2 * GP + tid + e * NT] = a[e];
 }
+static_assert(sizeof(float) * 64 * DNWV * 8 <= DNWV * 2 * DSTEP * D * 2, "the weights fit the V buffers");
 static_assert(2 * DSTEP * D * 2 >= 16 * (D + 2) * 4, "the waves' merge fits their V buffers");
 
 // grid (pairs, GP * D / 256): one output per thread; the loads of 32 chunks

@@ -98,3 +98,31 @@ def test_dense_masked_tokens(dtype, G):
             want = _softmax64(q[s], k[s, 0, keep], v[s, 0, keep])
             rel = np.linalg.norm(out[s] - want) / np.linalg.norm(want)
             assert rel < 2e-6, f"{dtype} G={G} mask {mask} of {a}..{b}: rel {rel:.2e}"
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_dense_infinite_values(dtype, G):
+    """An infinite element of V gives its infinity in its column (every weight
+    here is positive), two of opposite signs or a NaN give NaN, and the other
+    columns stay as they are (bound as above): at the first and last token, in
+    steps that the context ends in, in one of several runs."""
+    dt, inf = torch.float16 if dtype == "fp16" else torch.bfloat16, float("inf")
+    cases = [(1, {(0, 3): inf}), (33, {(32, 0): -inf}), (33, {(0, 127): inf, (31, 5): -inf}), (300, {(17, 9): inf, (299, 9): -inf}),
+             (300, {(299, 64): inf}), (2500, {(1500, 1): inf, (2499, 2): -inf}), (2500, {(3, 7): float("nan")}), (2500, {})]
+    S, n = len(cases), 2500
+    g = torch.Generator().manual_seed(11)
+    q, k, v = (torch.randn(*sh, 128, generator=g).to(dt) for sh in ((S, G), (S, 1, n), (S, 1, n)))
+    for s, (_, at) in enumerate(cases):
+        for (t, c), x in at.items():
+            v[s, 0, t, c] = x
+    lens = torch.tensor([L for L, _ in cases], dtype=torch.int32, device="cuda")
+    out = M.dense_decode(q.cuda(), k.cuda(), v.cuda(), lens, scale_of(), n, G).cpu().double().numpy()
+    for s, (L, at) in enumerate(cases):
+        want = _softmax64(q[s], k[s, 0, :L], v[s, 0, :L])
+        fin = np.isfinite(want)
+        assert (~fin).any(0).sum() == len({c for _, c in at})                # the reference itself: those columns only
+        where = f"{dtype} G={G} L={L} {at}"
+        assert np.array_equal(out[s][~fin], want[~fin], equal_nan=True), where
+        rel = np.linalg.norm(out[s][fin] - want[fin]) / np.linalg.norm(want[fin])
+        assert rel < 2e-6, f"{where}: rel {rel:.2e}"
