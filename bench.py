@@ -114,10 +114,16 @@ def algorithmic_bytes(cache, spec, nb_list, sel_list, desc_list):
                      fraction=round(sel_tok / max(scoreable_tok, 1), 5))
 
 
+# sources of the other paths' kernels; every other file of csrc takes part in the decode step
+OTHER_SOURCES = ("compress.hip", "dense.hip", "encode.hip", "rotation.hip")
+
+
 def source_hash():
     h = hashlib.sha256()
-    for f in ("attn.h", "decode.hip", "decode_common.h", "dense_step.h", "mosaic_internal.h", "score.hip"):
-        h.update(open(os.path.join(ROOT, "paper_2607_00760_amd", "csrc", f), "rb").read())
+    csrc = os.path.join(ROOT, "paper_2607_00760_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        if f.endswith((".hip", ".h")) and f not in OTHER_SOURCES:
+            h.update(f.encode() + b"\0" + open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()[:16]
 
 
