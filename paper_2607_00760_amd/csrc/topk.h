@@ -95,7 +95,7 @@ template <int KPT, int NW, typename Src>
 __device__ __forceinline__ void topk_reg(const Geom &g, const WsGeom &ws, const Src &src, int p, int nb, int ndesc, int budget,
                                          TopkSmem &sm) {
     constexpr int NT = 64 * NW;
-    constexpr int BPT = NW == 16 ? 2 : (NW == 1 ? 8 : 4), LB = NW == 16 ? 11 : (NW == 8 ? 11 : (NW == 4 ? 10 : 9));
+    constexpr int BPT = NW == 16 ? 2 : (NW == 4 ? 4 : 8), LB = NW == 16 ? 11 : (NW == 4 ? 10 : 9);
     static_assert(BPT * NT == 1 << LB && (1 << LB) <= TOPK_BINS, "bins of a pass");
     constexpr int BINS = 1 << LB;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;

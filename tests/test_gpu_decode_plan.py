@@ -1,8 +1,9 @@
 """Decode parity where the split plan, the scoring grid and the combine change
-form: more pairs or windows than the plan holds in registers, one to three
-windows (fused and two-kernel combine), 17 of them, selections of a few blocks,
-every block size with all channels kept, and update buffers of 1 to 31
-tokens.  Scores and selections bit for bit, outputs against the fp64 oracle
+form: the three plans (fixed on the host for caches of one window, in registers
+for up to 128 pairs of up to 16 windows, general beyond, and both of these for
+one-window batches too uneven for the fixed one), one to three windows (fused
+and two-kernel combine), selections of a few blocks, every block size with all
+channels kept, and update buffers of 1 to 31 tokens.  Scores and selections bit for bit, outputs against the fp64 oracle
 within the bound of the parity tests."""
 import numpy as np
 import pytest
@@ -15,8 +16,14 @@ pytestmark = pytest.mark.gpu
 
 MANY = tuple(70 + 37 * (i % 9) for i in range(33))              # 132 pairs of 4 kv heads
 CASES = {
-    "many_pairs": (dict(ctx=MANY, hkv=4), {}),
-    "at_128_pairs": (dict(ctx=MANY[:32], hkv=4, group=8), {}),
+    # three windows: the general plan, whose loops take the pairs 128 at a time, and the register plan's last
+    "many_pairs": (dict(ctx=MANY, hkv=4, rot_window=128), {}),
+    "at_128_pairs": (dict(ctx=MANY[:32], hkv=4, group=8, rot_window=128), {}),
+    "one_window_132_pairs": (dict(ctx=MANY, hkv=4), {}),
+    "one_window_128_pairs": (dict(ctx=MANY[:32], hkv=4, group=8), {}),
+    # a fixed plan would need more than four places for every workgroup the chip holds
+    "uneven_128_pairs": (dict(ctx=(6000,) + (70,) * 127, hkv=1), dict(select=(1, 1))),
+    "uneven_160_pairs": (dict(ctx=(70,) * 100 + (6000,) + (81,) * 59, hkv=1), dict(select=(1, 1))),
     "windows_1": (dict(ctx=(1000, 500), hkv=2, rot_window=4096), {}),
     "windows_2": (dict(ctx=(1000, 500), hkv=2, rot_window=640), {}),
     "windows_3": (dict(ctx=(1300, 500), hkv=2, rot_window=512), {}),
@@ -51,8 +58,13 @@ def test_decode_plan(name):
     ops = oracle_pairs(op, spec, lay, cap)
     c = gpu_cache(lp, spec, lay, cap)
     q = gen.make_queries(spec, 0)
+    c.workspace.zero_()
     out = c.decode(q.cuda(), scale_of())
     torch.cuda.synchronize()
+    # the plans made on the GPU leave their blocks per split behind the list header, the fixed one nothing
+    nw = c.layout.num_windows
+    planned = int(c.ws_region("wsel", 0, 4 * (nw + 3)).cpu().numpy().view(np.int32)[nw + 2]) > 0
+    assert planned == (nw > 1 or name.startswith("uneven")), f"{name}: another split plan than the case is for"
     want, sels, scores = oracle_decode_all(ops, spec, q, scale_of())
     for p in range(spec.num_seqs * spec.hkv):
         nb = ops[p].info().nblk

@@ -1,6 +1,8 @@
-"""Selections at the edges of the single-workgroup top-k's forms (1, 4, 8 and
-16 waves, 16 and 32 keys per thread) against the oracle, bit for bit: distinct
-scores, a few levels (ties at the threshold, some of them taken), all equal."""
+"""Selections at the edges of the single-workgroup top-k's forms (1, 4 and 16
+waves of 4 keys per thread, then 8, 16 and 32 keys), in the fused front kernel
+(every sequence at most 2048 blocks) and in the top-k kernel, against the
+oracle, bit for bit: distinct scores, a few levels (ties at the threshold, some
+of them taken), all equal."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("select", [(1, 10), (1, 2)])
-@pytest.mark.parametrize("blocks", [(16, 1008, 1024), (1040, 4096, 4112), (8192, 8208), (16384, 16400)])
+@pytest.mark.parametrize("blocks", [(16, 256, 272, 1008, 1024, 1040), (16, 256, 272, 1024, 4112), (1040, 4096, 4112), (8192, 8208), (16384, 16400)])
 def test_topk_edges(blocks, select):
     ctx = tuple(4 * b for b in blocks)
     spec = gen.spec("c1", ctx=ctx, hkv=1, rotate=False)
