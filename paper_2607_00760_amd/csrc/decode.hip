@@ -674,9 +674,19 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
         }
     }
     hipError_t e = hipSuccess;
-    if (fixed && g.nw == 1 && maxb <= FRONT_BLOCKS) {
+    const int cus = w.split_slots * ATTN_NWV / (4 * ATTN_WPE);
+    if (fixed && g.nw == 1 && maxb <= FRONT_BLOCKS && g.npairs <= cus) {
         // a short context: rotation, scores and selection of a pair by one
-        // workgroup (timed as the scoring)
+        // workgroup (timed as the scoring), as long as every pair has a compute
+        // unit to itself.  us a step with this kernel and with the three:
+        //   sequences of 8 kv heads    1 x 1000  1 x 8100  32 x 1000  32 x 8100
+        //     this                       28.9      39.4       41.3       64.9
+        //     the three                  33.0      41.2       46.6       74.6
+        //                             40 x 1000  40 x 8100  64 x 1000  128 x 1000
+        //     this                       57.6      85.1       67.5      122.8
+        //     the three                  53.0      91.2       64.0      100.0
+        // (2048 blocks are what its LDS holds.  The host counts a pair's blocks as
+        // its segments' smallest candidates, so a call may have far fewer.)
         if (ev) (void)hipEventRecord(ev[1], s);
         if ((e = launch_front(g, w, q, s)) != hipSuccess) return e;
         if (ev) (void)hipEventRecord(ev[2], s);

@@ -278,7 +278,7 @@ hipError_t launch_decode(const Geom &g, const WsGeom &w, const uint16_t *q, floa
                          int max_desc_used, int max_windows_used, hipStream_t s, hipEvent_t *ev);
 // the decode step's scoring and attention; fixed: every possible kept count is
 // 16, 32 or 48, small: none exceeds 48
-constexpr int FRONT_BLOCKS = 2048;     // blocks of a pair that the fused front kernel takes, at most
+constexpr int FRONT_BLOCKS = 2048;     // blocks of a pair that the fused front kernel takes, at most (its LDS)
 hipError_t launch_front(const Geom &g, const WsGeom &w, const uint16_t *q, hipStream_t s);
 hipError_t launch_score(const Geom &g, const WsGeom &w, int max_desc_used, bool fixed, bool small, hipStream_t s);
 hipError_t launch_attn_bf16_g4(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s);

@@ -286,8 +286,7 @@ __global__ void __launch_bounds__(256) k_score(Geom g, WsGeom ws, int spw) {
 // fetch, the round trip through memory); here the scores stay in LDS for the
 // selection.  What the attention and a caller's inspection read is written as
 // the separate kernels write it.  1 x 4117 tokens, 8 kv heads: 4.9 + 8.2 + 8.6
-// us apart, 18.0 together (8 requests of 1000 tokens: 20 and 13.8); beyond FRONT_BLOCKS a pair's keys are worth
-// more than one compute unit.
+// us apart, 18.0 together (8 requests of 1000 tokens: 20 and 13.8).
 constexpr int FRONT_SEGS = FRONT_BLOCKS / 4 + 2;
 
 struct TopkLds {

@@ -36,11 +36,13 @@ CASES = {
     "quest_b4_g8": (dict(ctx=(3000, 801, 40), hkv=1, group=8, dtype="bf16", rotate=False),
                     dict(force_default=True, default=(128, 1, 4), select=(1, 2))),
     "quest_b16_rotated": (dict(ctx=(5000, 64), hkv=1, dtype="bf16"), dict(force_default=True, default=(128, 1, 16))),
-    # the fused front kernel: its longest contexts (2048 blocks of 4, of 16), one block, mixed and
+    # the fused front kernel: its longest contexts (2048 blocks of 4, of 16), its most pairs, mixed and
     # truncated records, both group paddings, appended halves
     "front_b4_last": (dict(ctx=(8191, 8100), hkv=1), dict(force_default=True, default=(32, 1, 4))),
     "front_b16_last": (dict(ctx=(32767, 100), hkv=1, dtype="bf16"), dict(force_default=True, default=(32, 2, 16), block_cand=(16, 16, 16))),
     "front_first_past": (dict(ctx=(8256, 100), hkv=1), dict(force_default=True, default=(32, 1, 4))),
+    "front_256_pairs": (dict(ctx=tuple(40 + 3 * i for i in range(64)), hkv=4), {}),
+    "front_past_256_pairs": (dict(ctx=tuple(40 + 3 * i for i in range(65)), hkv=4), {}),
     "front_mixed_g7": (dict(ctx=(3000, 32, 64, 97), hkv=2, group=7, kind="outlier_random", dtype="bf16"), dict(tau_channel=0.2)),
     "front_trunc_g8": (dict(ctx=(2000, 1033), hkv=1, group=8), dict(trunc=96)),
     "front_unrotated": (dict(ctx=(1500, 33), hkv=1, group=1, rotate=False), dict(fp8=True)),

@@ -196,6 +196,20 @@ def test_every_failed_launch_is_reported(sim, name):
         assert st == HIP and message, f"{name}: call {i} ({what}) failed, status {st}"
 
 
+def test_front_kernel_takes_short_contexts_of_up_to_a_pair_per_compute_unit(sim):
+    for lens, hkv, want in (([1000] * 32, 8, True), ([40] * 256, 1, True), ([1000] * 33, 8, False), ([40] * 257, 1, False),
+                            ([8192], 8, True), ([8224], 8, False)):
+        sim.L.fake_reset(-1)
+        c = sim.cache(lens, num_kv_heads=hkv)
+        assert sim.compress(c) == OK
+        sim.L.fake_reset(-1)
+        assert sim.decode(c) == OK
+        names = [what for what, _ in sim.calls()]
+        assert sim.L.mosaic_cache_destroy(c["h"]) == OK
+        assert any("k_front" in x for x in names) == want, (lens[:1], len(lens), names)
+        assert any("k_topk" in x for x in names) != want
+
+
 # ---------------------------------------------------------------- the attention's grid
 SLOTS, SPLIT_MIN, SPLIT_MAX, SPLIT_FINE, SPLIT_LEAST = 1024, 48, 128, 16, 8     # 256 CUs, 4 workgroups each
 
