@@ -386,7 +386,7 @@ mosaic_status mosaic_decode_attention_noalloc(mosaic_cache *cache, const void *q
  *   ws            : at least mosaic_rotation_workspace_bytes bytes, 16-byte aligned
  * Arithmetic: fp32 covariance (exact 16-bit products, one chain per element
  * in token order per 4096-token slice, slices summed in order), cyclic Jacobi
- * in fp32 until the off-diagonal energy is below 1e-14 of the diagonal's.
+ * in fp32 until the off-diagonal energy is below 1e-12 of the diagonal's.
  * Errors: INVALID (NULL, misaligned, bad shape, small workspace), CAPACITY
  * (a context longer than max_tokens), UNSUPPORTED (head_dim != 128). */
 mosaic_status mosaic_rotation_workspace_bytes(const mosaic_params *params, int32_t num_seqs, int32_t max_tokens,
@@ -453,8 +453,9 @@ mosaic_status mosaic_cache_stats(const mosaic_cache *cache, mosaic_stats *out, v
  * HIP events on its stream around each of its kernels (no device memory is
  * allocated).  mosaic_decode_timing waits for the last timed decode and writes
  * its kernel times in milliseconds to ms[0..4] = q rotation, block scoring,
- * top-k, split-K attention, reduce.  Errors: STATE (timing off or no decode
- * yet), HIP. */
+ * top-k, split-K attention, reduce.  Short contexts (one rotation window) take
+ * the first three in one kernel: its time is in ms[1], and ms[0] and ms[2] hold
+ * the gaps between events.  Errors: STATE (timing off or no decode yet), HIP. */
 mosaic_status mosaic_set_timing(mosaic_cache *cache, int32_t enable);
 mosaic_status mosaic_decode_timing(mosaic_cache *cache, float *ms);
 

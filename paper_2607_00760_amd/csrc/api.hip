@@ -594,7 +594,7 @@ mosaic_status mosaic_dense_decode_attention(const void *q, const void *k, const 
     const size_t need = dense_part_bytes(num_seqs * num_kv_heads, group_size, max_ctx);
     if (ws_bytes < need) return fail(MOSAIC_ERR_INVALID, "workspace %zu < %zu", ws_bytes, need);
     hipError_t e = launch_dense((const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v, out, num_seqs,
-                                num_kv_heads, group_size, dtype, seq_stride, max_ctx, ctx_lens, sm_scale, (float *)ws, 0,
+                                num_kv_heads, group_size, dtype, seq_stride, max_ctx, ctx_lens, sm_scale, (float *)ws,
                                 (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "dense launch");
     return ok();

@@ -25,17 +25,24 @@ namespace {
 // pair's token arena, and r << 8 | log2g << 16 | log2b << 20
 typedef uint2 BlkInfo;
 
-// Split-K plan of a call.  The selected blocks of all pairs are spread over
-// the attention workgroups that the device runs at once (split_slots), so
-// that the attention runs as one round of workgroups: bps blocks per split,
-// bps = ceil(selected blocks / slots left once every non-empty window and
-// every update buffer has its rounding split), within [SPLIT_MIN,
-// SPLIT_MAX].  Window w of a pair with n selected entries gets ceil(n / bps)
-// splits dealt round-robin, so every split of a window holds the same mix of
-// 16-, 8- and 4-token blocks (the list is in block order, where blocks of one
-// size cluster); a pair's splits are its windows' in order, then one for its
-// update buffer.  Every kernel that numbers splits derives the same plan from
-// the top-k's window bounds.  List bounds are clamped to [0, lim] (the list's
+// Split-K plan of a call.  A window of a pair with n selected entries gets
+// ceil(n / bps) splits of at most bps blocks, dealt round-robin, so every split of
+// a window holds the same mix of 16-, 8- and 4-token blocks (the list is in block
+// order, where blocks of one size cluster); a pair's splits are its windows' in
+// order, then one for its update buffer.  Three plans, one numbering:
+//   fixed     (caches of one window, unless very uneven; planned by the host,
+//             fixed_splits): each pair's tokens in shares of the same size, at
+//             least 128, of at most SPLIT_MAX blocks; a workgroup needs its own
+//             pair's counts only;
+//   register  (up to 128 pairs of up to 16 windows, plan_small): one bps for the
+//             call, such that the splits fill whole rounds of the workgroups that
+//             the device runs at once (split_slots, less a rounding split for
+//             every non-empty window and buffer), from about 128 tokens to
+//             SPLIT_MAX blocks;
+//   general   (beyond, split_blocks): one bps for the call, one round, within
+//             [SPLIT_MIN, SPLIT_MAX].
+// The combine takes the fixed plan's numbers from the same function, the others'
+// bps from pair 0's list header.  List bounds are clamped to [0, lim] (the list's
 // capacity), so that no workspace content can send an index outside it.
 
 // f(n) for the selected entries n of each window of a pair, in window order

@@ -10,13 +10,11 @@ constexpr int D = 128;        // head dim
 constexpr int SEG = 64;       // strategy segment (tokens)
 constexpr int UBUF = 32;      // update buffer (tokens)
 constexpr int WAVE = 64;
-// selected blocks per split-K partition: chosen per call between these bounds
-// (the fewest sizes the per-pair partial arrays, the most the attention's
-// block table)
-constexpr int SPLIT_MIN = 48;
-constexpr int SPLIT_MAX = 128;
-constexpr int SPLIT_FINE = 16;    // the same where the selections are short (smaller workspaces have room for it)
-constexpr int SPLIT_LEAST = 8;    // blocks of the smallest split (short selections; see the attention's plan)
+// selected blocks per split-K partition, chosen per call
+constexpr int SPLIT_MAX = 128;    // at most (the attention's block table)
+constexpr int SPLIT_MIN = 48;     // at least in the general plan; what the per-pair partial arrays of large workspaces hold
+constexpr int SPLIT_FINE = 16;    // what those of smaller workspaces hold: splits of a full selection; shorter ones
+constexpr int SPLIT_LEAST = 8;    // go down to this many blocks in the other plans, where about 128 tokens are fewer
 constexpr int ATTN_NWV = 2;       // waves per attention workgroup
 constexpr int ATTN_WPE = 2;       // waves per SIMD the attention's registers allow
 constexpr int MAX_WINDOWS = 1024;  // rotation windows per sequence (the selection tracks them in LDS)
@@ -287,7 +285,7 @@ hipError_t launch_attn_fp16_g4(const Geom &g, const WsGeom &w, float scale, cons
 hipError_t launch_attn_fp16_g8(const Geom &g, const WsGeom &w, float scale, const uint16_t *q, bool fixed, bool small, hipStream_t s);
 hipError_t launch_dense(const uint16_t *q, const uint16_t *k, const uint16_t *v, float *out, int nseq,
                         int hkv, int G, int dtype, int64_t seq_stride, int max_ctx, const int32_t *ctx,
-                        float scale, float *part, int max_splits, hipStream_t s);
+                        float scale, float *part, hipStream_t s);
 
 size_t dense_part_bytes(int npairs, int G, int max_ctx);
 size_t rotation_ctx_bytes(int num_seqs);

@@ -196,7 +196,6 @@ __global__ void __launch_bounds__(256) k_score(Geom g, WsGeom ws, int spw) {
                 if (valid) {
                     out[d.first_block + j] = best;
                     binfo[d.first_block + j] = info_of(d, j);
-            bsize[d.first_block + j] = d.log2b;
                     bsize[d.first_block + j] = d.log2b;
                 }
             }

@@ -78,7 +78,7 @@ hipError_t launch_decode(const Geom &g, const WsGeom &, const uint16_t *, float 
     return hipSuccess;
 }
 hipError_t launch_dense(const uint16_t *, const uint16_t *, const uint16_t *, float *, int nseq, int hkv, int G,
-                        int, int64_t, int, const int32_t *, float, float *, int, hipStream_t) {
+                        int, int64_t, int, const int32_t *, float, float *, hipStream_t) {
     rec("dense nseq=%d hkv=%d G=%d", nseq, hkv, G);
     return hipSuccess;
 }
