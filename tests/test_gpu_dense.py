@@ -126,3 +126,25 @@ def test_dense_infinite_values(dtype, G):
         assert np.array_equal(out[s][~fin], want[~fin], equal_nan=True), where
         rel = np.linalg.norm(out[s][fin] - want[fin]) / np.linalg.norm(want[fin])
         assert rel < 2e-6, f"{where}: rel {rel:.2e}"
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_dense_long_runs(dtype):
+    """512 pairs of up to 4096 tokens: more than 1024 chunks, so runs of two, at
+    the edges of a run (bound as above)."""
+    dt, S, H, G, n = (torch.float16 if dtype == "fp16" else torch.bfloat16), 64, 8, 4, 4096
+    lens = [(2047, 2048, 2049, 4096, 0, 1, 3000, 4095)[s % 8] for s in range(S)]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    k = torch.randn(S, H, n, 128, generator=g, device="cuda", dtype=torch.float32).to(dt)
+    v = torch.randn(S, H, n, 128, generator=g, device="cuda", dtype=torch.float32).to(dt)
+    q = torch.randn(S, H * G, 128, generator=g, device="cuda").to(dt)
+    out = M.dense_decode(q, k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"), scale_of(), n, G).cpu().double().numpy()
+    for s, L in enumerate(lens):
+        for h in range(0, H, 3):
+            got = out[s, h * G: (h + 1) * G]
+            if L == 0:
+                assert not got.any()
+                continue
+            want = _softmax64(q[s, h * G: (h + 1) * G].cpu(), k[s, h, :L].cpu(), v[s, h, :L].cpu())
+            rel = np.linalg.norm(got - want) / np.linalg.norm(want)
+            assert rel < 2e-6, f"{dtype} sequence {s} head {h} L={L}: rel {rel:.2e}"
