@@ -918,17 +918,17 @@ hipError_t attn_dt(const Geom &g, const WsGeom &w, float scale, const uint16_t *
     // larger than the plan that the kernel takes can need.  The register plan
     // has as many splits as whole rounds of the resident workgroups, the general
     // one as fill a single round or as splits of SPLIT_MAX blocks, both with one
-    // rounding split more per window and buffer; and never more than every pair's
-    // whole partial array or the most blocks that can be selected in splits of
-    // SPLIT_LEAST.  (Sized by rounds for both, and by a round more than needed,
-    // one sequence of 60000 tokens beside 31 of 500 launched 7680 workgroups of
-    // the general plan, 82 us in this kernel; 3584 take 46.)
+    // rounding split more per window and buffer; and never more than the most
+    // blocks that can be selected in splits of the plan's least size, or than
+    // every pair's whole partial array.  (Sized by rounds for both, and by a round
+    // more than needed, one sequence of 60000 tokens beside 31 of 500 launched
+    // 7680 workgroups of the general plan, 82 us in this kernel; 3584 take 46.)
     const size_t smem = ATTN_HDR_BYTES + (size_t)ATTN_NWV * TILE_BYTES;
     const long long extra = (long long)g.npairs * (g.nw + 1);
     const long long most = (long long)g.npairs * ceil_div(w.max_sel, SPLIT_MAX);
     const long long room = std::max<long long>(std::max<long long>(w.split_slots - extra, w.split_slots / 4), 1);    // (the plan's, at least)
     const long long whole = register_plan(g) ? (most + room - 1) / room * w.split_slots : std::max<long long>(w.split_slots, most);
-    const long long least = (long long)g.npairs * ceil_div(w.max_sel, SPLIT_LEAST);
+    const long long least = (long long)g.npairs * ceil_div(w.max_sel, register_plan(g) ? SPLIT_LEAST : SPLIT_MIN);
     const long long nwg = std::min<long long>(std::min(whole, least) + extra, (long long)g.npairs * w.max_splits);
     const unsigned grid = w.fix_splits ? (unsigned)(g.npairs * (w.fix_splits + 1)) : (unsigned)nwg;
     auto go = [&](auto kernel) {

@@ -239,7 +239,7 @@ GRIDS = {
     "long_one_room": ([(1 << 20) + 64], 8, 65536), "uneven_many": ([60000] + [500] * 31, 8, 65536),
     "uneven_many_two_windows": ([100000] + [100] * 31, 8, 65536), "at_128_pairs": ([9000 + 70 * i for i in range(32)], 4, 4096),
     "past_128_pairs": ([9000 + 70 * i for i in range(33)], 4, 4096), "windows_16": ([16000], 8, 1024), "windows_17": ([17000], 8, 1024),
-    "short_many": ([40 + i for i in range(64)], 8, 64), "short_few": ([1000, 333], 2, 512),
+    "short_many": ([40 + i for i in range(64)], 8, 64), "short_133_pairs": ([600 - i for i in range(33)], 4, 448), "short_few": ([1000, 333], 2, 512),
 }
 
 
@@ -278,3 +278,5 @@ def test_attention_grid_covers_the_plan_and_little_more(sim, name):
     full = npairs * -(-max_sel // SPLIT_MAX)
     rounds = -(-full // max(SLOTS - extra, SLOTS // 4)) if small else 1
     assert grid <= max(rounds * SLOTS, 0 if small else full) + extra, f"{name}: {grid} workgroups"
+    # and its splits' least size
+    assert grid <= npairs * -(-max_sel // (SPLIT_LEAST if small else SPLIT_MIN)) + extra, f"{name}: {grid} workgroups"
