@@ -479,9 +479,11 @@ k_attn(Geom g, WsGeom ws, float scale, const uint16_t *qraw) {
         float z[GP];
 #pragma unroll
         for (int h = 0; h < GP; ++h) z[h] = 0.0f;
-#pragma unroll
+        // (eight heads: a piece at a time, all of a row's reads of q at once would spill)
+#pragma unroll (GP == 8 ? 1 : 4)
         for (int x = 0; x < 4; ++x) {
-            const uint32_t w4[4] = {kr[x].x, kr[x].y, kr[x].z, kr[x].w};
+            const uint32_t w4[4] = {kr[0].x, kr[0].y, kr[0].z, kr[0].w};
+            kr[0] = kr[1]; kr[1] = kr[2]; kr[2] = kr[3];    // (a runtime index would put them in memory)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float kv = h2f_t<DT>((e & 1) ? (w4[e >> 1] >> 16) : (w4[e >> 1] & 0xffffu));
