@@ -219,9 +219,9 @@ mosaic_status mosaic_workspace_bytes(const mosaic_cache *cache, int32_t op, size
  *                              block of 16 output columns and each window
  *                              (the last slot: the update buffer), the
  *                              window's merged max and sum per head and its
- *                              back-rotated output columns (not written for
- *                              caches of one or two windows, whose combine
- *                              merges them itself)
+ *                              back-rotated output columns (may be left as it
+ *                              is for caches of one or two windows, whose
+ *                              combine can merge them itself)
  * Calls that overlap on one workspace race; separate streams need separate
  * workspaces. */
 typedef struct {

@@ -720,8 +720,13 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
     else e = GP == 4 ? launch_attn_fp16_g4(g, w, scale, q, fixed, small, s) : launch_attn_fp16_g8(g, w, scale, q, fixed, small, s);
     if (e != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[4], s);
+    // Few slots per output: one kernel.  Three slots of eight heads are 12 waves of
+    // 118 registers, one workgroup per compute unit: that form is for two rounds
+    // of them at most.  us of the merge fused / apart, groups of 8, two windows:
+    //   pairs   8          64           128          264          560
+    //         8.9 / 11.2  14.2 / 16.0  23.9 / 22.3  46.9 / 35.7  88.8 / 63.4
     const int wgs = (g.npairs + 7) / 8 * 8 * CMB_NCC;
-    if (g.nw <= 2) {                           // few slots per output: one kernel
+    if (g.nw == 1 || (g.nw == 2 && (GP == 4 || wgs <= 2 * cus))) {
         if (g.nw == 1) hipLaunchKernelGGL((k_combine<GP, 2>), dim3(wgs), dim3(2 * CMB_THREADS), 0, s, g, w, out);
         else hipLaunchKernelGGL((k_combine<GP, 3>), dim3(wgs), dim3(3 * CMB_THREADS), 0, s, g, w, out);
         if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -2,7 +2,7 @@
 form: the three plans (fixed on the host for caches of one window, in registers
 for up to 128 pairs of up to 16 windows, general beyond, and both of these for
 one-window batches too uneven for the fixed one), one to three windows (fused
-and two-kernel combine), selections of a few blocks, every block size with all
+and two-kernel combine, for two windows of eight heads by the number of pairs), selections of a few blocks, every block size with all
 channels kept, and update buffers of 1 to 31 tokens.  Scores and selections bit for bit, outputs against the fp64 oracle
 within the bound of the parity tests."""
 import numpy as np
@@ -26,6 +26,8 @@ CASES = {
     "uneven_160_pairs": (dict(ctx=(70,) * 100 + (6000,) + (81,) * 59, hkv=1), dict(select=(1, 1))),
     "windows_1": (dict(ctx=(1000, 500), hkv=2, rot_window=4096), {}),
     "windows_2": (dict(ctx=(1000, 500), hkv=2, rot_window=640), {}),
+    "windows_2_g8_64_pairs": (dict(ctx=tuple(60 + 11 * i for i in range(16)), hkv=4, group=8, rot_window=128), {}),
+    "windows_2_g8_68_pairs": (dict(ctx=tuple(60 + 11 * i for i in range(17)), hkv=4, group=7, rot_window=128), {}),
     "windows_3": (dict(ctx=(1300, 500), hkv=2, rot_window=512), {}),
     "windows_16": (dict(ctx=(1000, 70), hkv=2, rot_window=64), dict(select=(1, 3))),
     "windows_17": (dict(ctx=(1080, 70), hkv=2, rot_window=64), dict(select=(1, 3))),

@@ -210,6 +210,20 @@ def test_front_kernel_takes_short_contexts_of_up_to_a_pair_per_compute_unit(sim)
         assert any("k_topk" in x for x in names) != want
 
 
+def test_combine_of_two_windows_is_one_kernel_while_its_workgroups_fit_two_rounds(sim):
+    # groups of up to four heads always; of eight at most 512 workgroups of 16 columns, 64 pairs
+    for group, seqs, W, want in ((4, 9, 128, True), (8, 8, 128, True), (8, 9, 128, False), (5, 16, 128, False), (8, 16, 256, True),
+                                 (4, 2, 64, False)):
+        sim.L.fake_reset(-1)
+        c = sim.cache([250] * seqs, num_kv_heads=8, group_size=group, rot_window=W)
+        assert sim.compress(c) == OK
+        sim.L.fake_reset(-1)
+        assert sim.decode(c) == OK
+        names = [what for what, _ in sim.calls()]
+        assert sim.L.mosaic_cache_destroy(c["h"]) == OK
+        assert any("k_merge" in x for x in names) != want, (group, seqs, W, names)
+
+
 # ---------------------------------------------------------------- the attention's grid
 SLOTS, SPLIT_MIN, SPLIT_MAX, SPLIT_FINE, SPLIT_LEAST = 1024, 48, 128, 16, 8     # 256 CUs, 4 workgroups each
 
