@@ -363,9 +363,12 @@ __global__ void __launch_bounds__(1024) k_front(Geom g, WsGeom ws, const uint16_
         const int x0 = b - (int)d.first_block;
         const int rk = valid ? d.r : 0, l2g = d.log2g;
         const uint8_t *rec = valid ? sc + d.sc_off + (uint32_t)x0 * (uint32_t)vec_bytes(rk, l2g, g.trunc) : sc;
-        const bool a16 = __all(!valid || (l2g == 0 && ((uintptr_t)rec & 15u) == 0 && g.trunc == D));
+        // whole 16-byte granules wherever bitmap and values are 4-byte aligned (what
+        // lies past a record is read inside the arena's slack and never used)
+        const int bmb = valid ? bm_bytes(l2g, g.trunc) : 0;
         PVec<48> x;
-        load_pvec<48, -1, true>(x, rec, rec + bm_bytes(l2g, g.trunc), wave_max_i(rk), a16);
+        if (__all((((uintptr_t)rec | (uintptr_t)bmb) & 3u) == 0)) load_pvec<48, 1, false, 6>(x, rec, rec + bmb, 48, true);
+        else load_pvec<48, 0, true>(x, rec, rec + bmb, wave_max_i(rk), false);
         if (g.trunc < D) mask_words(x.bw, g.trunc >> l2g);
         float acc[GP];
 #pragma unroll

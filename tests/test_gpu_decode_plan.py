@@ -47,6 +47,8 @@ CASES = {
     "front_past_256_pairs": (dict(ctx=tuple(40 + 3 * i for i in range(65)), hkv=4), {}),
     "front_mixed_g7": (dict(ctx=(3000, 32, 64, 97), hkv=2, group=7, kind="outlier_random", dtype="bf16"), dict(tau_channel=0.2)),
     "front_trunc_g8": (dict(ctx=(2000, 1033), hkv=1, group=8), dict(trunc=96)),
+    "front_trunc_b4_g7": (dict(ctx=(8100, 33), hkv=1, group=7, dtype="bf16"), dict(force_default=True, default=(16, 1, 4), trunc=96)),
+    "front_trunc_32": (dict(ctx=(2500, 64), hkv=2), dict(trunc=32, keep_cand=(16, 32, 32), tau_channel=0.2)),
     "front_unrotated": (dict(ctx=(1500, 33), hkv=1, group=1, rotate=False), dict(fp8=True)),
     "some_keep_all": (dict(ctx=(1500, 900), hkv=2), dict(keep_cand=(16, 64, 128), default=(128, 1, 8), tau_channel=0.01)),
 }
