@@ -453,36 +453,48 @@ __global__ void __launch_bounds__(CMB_THREADS * NS) k_combine(Geom g, WsGeom ws,
     auto &wsc = wsc_s[grp];
     const int oi = tid / NPART, part_i = tid % NPART;         // output (head, column) and channel part
     const int oh = oi / CMB_COLS, oj = oi % CMB_COLS;
-    // R_v[c][j0 .. j0 + 15], loaded before it is known whether the slot has splits
-    const bool turn = w < g.nw && g.rotated;
+    // R_v[c][j0 .. j0 + 15], loaded before it is known whether the slot has
+    // splits, unless its window holds no token (a cache of 64 windows that holds
+    // 32 x 1000 tokens would read 512 MB of rotations for nothing)
+    const PairMeta meta = *g.meta_of(p);
+    const bool turn = w < g.nw && g.rotated && (NS > 1 || (g.dyn ? w < meta.nwin : (long long)w * g.W < meta.L));
     float4 rq0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), rq1 = rq0;
     if (turn) {
         const float4 *rvt = (const float4 *)(g.rot_of(p, w) + D * D + (uint64_t)j0 * D);
         rq0 = rvt[tid];
         rq1 = rvt[tid + CMB_THREADS];
     }
-    const PairMeta meta = *g.meta_of(p);
     int nf, prov, nbuf;
     pair_ndesc(meta, nf, prov, nbuf);
     const int32_t *wsel = ws.wsel + (uint64_t)p * (ws.wsel_stride / 4);
     const float *part = ws.part + (uint64_t)p * (ws.part_stride / 4);
     const int lim = ws.max_blocks;
+    float *res = ws.wres + (uint64_t)p * (ws.wres_stride / 4) + ((uint64_t)cc * (g.nw + 1) + w) * (GP * CMB_RES);
     // this slot's splits: the windows' splits are numbered window by window,
     // then the buffer's (the attention's numbering), s0 = those before it
     int s0 = 0, nsp = 0, most = 0;                            // most: splits of the largest slot (the rounds they share)
     // the attention's plan (blocks per split, or one window's fixed splits)
     const int bps = NS == 2 && ws.fix_splits ? 1 : min(max(ws.wsel[g.nw + 2], SPLIT_LEAST), SPLIT_MAX);
-    for (int x = 0; x <= (NS > 1 ? g.nw - 1 : min(w, g.nw - 1)); ++x) {
-        const int a = min(max(wsel[x], 0), lim), b = min(max(wsel[x + 1], a), lim);
-        const int n = NS == 2 && ws.fix_splits ? fixed_splits(g, ws, meta.L, b - a) : (b - a + bps - 1) / bps;
-        if (x < w) s0 += n; else if (x == w) nsp = n;
-        most = max(most, n);
+    if (NS == 1) {                                            // a lane per window (one after the other, most of an empty slot's time)
+        const int lane = tid & 63, last = min(w, g.nw - 1);
+        for (int x0 = 0; x0 <= last; x0 += 64) {
+            const int x = x0 + lane, a = x <= last ? min(max(wsel[x], 0), lim) : 0, b = x <= last ? min(max(wsel[x + 1], a), lim) : 0;
+            const uint32_t n = (uint32_t)((b - a + bps - 1) / bps);
+            s0 += (int)__builtin_amdgcn_readlane((int)wave_scan_add(x < w ? n : 0u), 63);
+            if (w >= x0 && w < x0 + 64) nsp = (int)__builtin_amdgcn_readlane((int)n, w - x0);
+        }
+    } else {
+        for (int x = 0; x < g.nw; ++x) {
+            const int a = min(max(wsel[x], 0), lim), b = min(max(wsel[x + 1], a), lim);
+            const int n = NS == 2 && ws.fix_splits ? fixed_splits(g, ws, meta.L, b - a) : (b - a + bps - 1) / bps;
+            if (x < w) s0 += n; else if (x == w) nsp = n;
+            most = max(most, n);
+        }
     }
     if (w == g.nw) nsp = nbuf > 0 ? 1 : 0;
     if (s0 + nsp > ws.max_splits) nsp = 0;                    // (cannot happen: the attention had this many)
     if (NS > 1) { most = max(most, 1); } else most = nsp;
     const bool rot = turn && nsp > 0;
-    float *res = ws.wres + (uint64_t)p * (ws.wres_stride / 4) + ((uint64_t)cc * (g.nw + 1) + w) * (GP * CMB_RES);
     if (NS > 1 || nsp > 0) {
         float A[NE];
 #pragma unroll

@@ -31,6 +31,8 @@ CASES = {
     "windows_3": (dict(ctx=(1300, 500), hkv=2, rot_window=512), {}),
     "windows_16": (dict(ctx=(1000, 70), hkv=2, rot_window=64), dict(select=(1, 3))),
     "windows_17": (dict(ctx=(1080, 70), hkv=2, rot_window=64), dict(select=(1, 3))),
+    "windows_64": (dict(ctx=(4092, 70), hkv=1, rot_window=64), dict(select=(1, 3))),
+    "windows_70_mostly_empty": (dict(ctx=(300, 4476, 33), hkv=1, group=8, rot_window=64), {}),
     "buffers": (dict(ctx=(1, 31, 33, 63, 65, 95, 97, 127), hkv=1, group=7, dtype="bf16"), {}),
     "few_blocks_b16": (dict(ctx=(9000, 129), hkv=1), dict(force_default=True, default=(32, 1, 16))),
     "all_selected_b4": (dict(ctx=(4000, 33), hkv=1), dict(force_default=True, default=(16, 2, 4), select=(1, 1))),
