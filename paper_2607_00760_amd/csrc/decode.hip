@@ -475,7 +475,7 @@ __global__ void __launch_bounds__(CMB_THREADS * NS) k_combine(Geom g, WsGeom ws,
     int s0 = 0, nsp = 0, most = 0;                            // most: splits of the largest slot (the rounds they share)
     // the attention's plan (blocks per split, or one window's fixed splits)
     const int bps = NS == 2 && ws.fix_splits ? 1 : min(max(ws.wsel[g.nw + 2], SPLIT_LEAST), SPLIT_MAX);
-    if (NS == 1) {                                            // a lane per window (one after the other, most of an empty slot's time)
+    if (NS == 1 && g.nw > 2) {                                // a lane per window (one after the other, most of an empty slot's time)
         const int lane = tid & 63, last = min(w, g.nw - 1);
         for (int x0 = 0; x0 <= last; x0 += 64) {
             const int x = x0 + lane, a = x <= last ? min(max(wsel[x], 0), lim) : 0, b = x <= last ? min(max(wsel[x + 1], a), lim) : 0;
@@ -484,7 +484,7 @@ __global__ void __launch_bounds__(CMB_THREADS * NS) k_combine(Geom g, WsGeom ws,
             if (w >= x0 && w < x0 + 64) nsp = (int)__builtin_amdgcn_readlane((int)n, w - x0);
         }
     } else {
-        for (int x = 0; x < g.nw; ++x) {
+        for (int x = 0; x <= (NS > 1 ? g.nw - 1 : min(w, g.nw - 1)); ++x) {
             const int a = min(max(wsel[x], 0), lim), b = min(max(wsel[x + 1], a), lim);
             const int n = NS == 2 && ws.fix_splits ? fixed_splits(g, ws, meta.L, b - a) : (b - a + bps - 1) / bps;
             if (x < w) s0 += n; else if (x == w) nsp = n;
@@ -692,11 +692,11 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
         // workgroup (timed as the scoring), as long as every pair has a compute
         // unit to itself.  us a step with this kernel and with the three:
         //   sequences of 8 kv heads    1 x 1000  1 x 8100  32 x 1000  32 x 8100
-        //     this                       28.9      39.4       41.3       64.9
-        //     the three                  33.0      41.2       46.6       74.6
+        //     this                       28.4      39.3       40.6       64.2
+        //     the three                  32.2      40.8       46.4       73.8
         //                             40 x 1000  40 x 8100  64 x 1000  128 x 1000
-        //     this                       57.6      85.1       67.5      122.8
-        //     the three                  53.0      91.2       64.0      100.0
+        //     this                       56.8      83.9       66.1      119.9
+        //     the three                  52.1      90.6       62.6       98.4
         // (2048 blocks are what its LDS holds.  The host counts a pair's blocks as
         // its segments' smallest candidates, so a call may have far fewer.)
         if (ev) (void)hipEventRecord(ev[1], s);
