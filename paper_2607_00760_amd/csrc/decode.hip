@@ -736,7 +736,7 @@ hipError_t launch_decode_gp(const Geom &g, const WsGeom &w_in, const uint16_t *q
     // 118 registers, one workgroup per compute unit: that form is for two rounds
     // of them at most.  us of the merge fused / apart, groups of 8, two windows:
     //   pairs   8          64           128          264          560
-    //         8.9 / 11.2  14.2 / 16.0  23.9 / 22.3  46.9 / 35.7  88.8 / 63.4
+    //         9.0 / 11.6  14.1 / 16.2  23.6 / 22.1  47.1 / 36.1  89.8 / 63.5
     const int wgs = (g.npairs + 7) / 8 * 8 * CMB_NCC;
     if (g.nw == 1 || (g.nw == 2 && (GP == 4 || wgs <= 2 * cus))) {
         if (g.nw == 1) hipLaunchKernelGGL((k_combine<GP, 2>), dim3(wgs), dim3(2 * CMB_THREADS), 0, s, g, w, out);
